@@ -4,24 +4,26 @@
 // buffers. For callers that cannot allocate: code under HIP graph capture, serving loops,
 // harnesses that forbid hipMalloc.
 //
-// The same kernels as the context's step do the work (LDS-privatised fixed-point deposit,
-// the three forward transform passes with the FP64 bin sums of the last one, the bin power
-// reduction). What a context computes once on the host at init (bin table, mode counts,
-// twiddles) is rebuilt here on every call by one setup workgroup, from edges and twiddles
-// passed by value, so the call needs no host-to-device copy either.
+// The same kernels as the context's step do the work (LDS-privatised fixed-point deposit, the
+// forward transform passes with the FP64 bin sums of the last one). What a context computes
+// once on the host at init (bin table, mode counts, twiddles) is rebuilt here on every call,
+// from edges and twiddles passed by value, so the call needs no host-to-device copy either:
+// the tables by the kernel that clears the density, each bin's mode count by the workgroup
+// that sums its power. Five launches; a box of 64^3 is bound by their latencies.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
-#include "pm_nu_internal.hpp"
+#include "response_device.hpp"
 
 namespace pmnu {
 namespace {
 
 constexpr int kStaticMaxMesh = 64;     // largest N
 constexpr int kStaticMaxBins = 256;    // largest B
-constexpr int64_t kStaticBytes = 5 << 20;   // 5 MiB; the N = 64, B = 256 layout needs 4.3 MiB
+constexpr int64_t kStaticBytes = 5 << 20;   // 5 MiB; the N = 64, B = 256 layout needs 3.3 MiB
 constexpr int kMaxDevices = 64;
 
 // The scratch of every call on this device (each device holds its own copy). In host code
@@ -36,36 +38,68 @@ struct StaticTables {
   float2 tw[kStaticMaxMesh];          // exp(-2 pi i m / N)
 };
 
-// Bin of every integer |n|^2 (as the context's host table), the twiddles, and the full-sphere
-// mode count of every bin (exact integer counts over the triples of [-N/2, N/2)^3).
-__global__ __launch_bounds__(1024) void static_setup_kernel(StaticTables t, int n, int nbins,
-                                                            int n2max, uint16_t* __restrict__ bin_of_n2,
-                                                            float2* __restrict__ tw,
-                                                            double* __restrict__ counts) {
-  __shared__ uint16_t s_bin[3 * kStaticMaxMesh * kStaticMaxMesh / 4 + 1];
-  __shared__ int s_cnt[kStaticMaxBins];
-  const int tid = threadIdx.x;
-  for (int b = tid; b < nbins; b += blockDim.x) s_cnt[b] = 0;
-  for (int m = tid; m < n; m += blockDim.x) tw[m] = t.tw[m];
-  for (int n2 = tid; n2 <= n2max; n2 += blockDim.x) {
+// The density cleared by every workgroup; the first ones also write the bin of every integer
+// |n|^2 (as the context's host table) and the twiddles. One launch of N^3 / 1024 workgroups
+// (each thread clears two nodes) instead of a table kernel of one workgroup, which also
+// counted the modes there (112 us at N = 64, of 140 for the call), and two fills.
+__global__ __launch_bounds__(512) void static_setup_kernel(StaticTables t, int n, int nbins,
+                                                           int n2max,
+                                                           uint16_t* __restrict__ bin_of_n2,
+                                                           float2* __restrict__ tw,
+                                                           ulonglong2* __restrict__ rho,
+                                                           int64_t n_pairs) {
+  const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (gid < n_pairs) rho[gid] = make_ulonglong2(0ull, 0ull);
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  for (int64_t i = gid; i <= n2max; i += stride) {
+    const int n2 = static_cast<int>(i);
     int lo = 0, hi = nbins - 1;        // the last b with edges[b] <= n2, at most nbins - 1
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (t.edges[mid] <= n2) lo = mid; else hi = mid - 1;
     }
-    const uint16_t b = static_cast<uint16_t>(n2 == 0 ? 0 : lo);
-    s_bin[n2] = b;
-    bin_of_n2[n2] = b;
+    bin_of_n2[n2] = static_cast<uint16_t>(n2 == 0 ? 0 : lo);
+    if (n2 < n) tw[n2] = t.tw[n2];       // n <= n2max = 3 n^2 / 4 from n = 2 on
   }
-  __syncthreads();
-  const int h = n / 2, m3 = n * n * n;
-  for (int t3 = tid; t3 < m3; t3 += blockDim.x) {
-    const int i = t3 / (n * n) - h, j = (t3 / n) % n - h, l = t3 % n - h;
-    const int n2 = i * i + j * j + l * l;
-    if (n2 > 0) atomicAdd(&s_cnt[s_bin[n2]], 1);
+}
+
+// Number of l in [-h, h) with l^2 < t.
+__device__ __forceinline__ int lines_below(int t, int h) {
+  if (t <= 0) return 0;
+  int s = static_cast<int>(sqrtf(static_cast<float>(t - 1)));   // t <= 3 kStaticMaxMesh^2 / 4 + 1
+  while (s * s > t - 1) --s;
+  while ((s + 1) * (s + 1) <= t - 1) ++s;
+  return s >= h ? 2 * h : 2 * s + 1;
+}
+
+// P_cdm of bin b from the partial sums of the forward transform, with the bin's full-sphere
+// mode count taken here: the triples (i, j, l) of [-h, h)^3 with |n|^2 in the bin, as pairs
+// (|i|, |j|) <= h with their multiplicity (1 for 0 and h, which only -h has; 2 between) times
+// the number of l. (h + 1)^2 pairs over 256 threads are at most five each, exact integers.
+__global__ __launch_bounds__(256) void static_power_kernel(StaticTables t, int n, int nbins,
+                                                           const double* __restrict__ partial,
+                                                           int n_partial, double norm,
+                                                           double* __restrict__ pcdm) {
+  __shared__ double red[256 / 64];
+  __shared__ int s_cnt;
+  const int b = blockIdx.x, h = n / 2, tid = threadIdx.x;
+  if (tid == 0) s_cnt = 0;
+  const int e0 = t.edges[b], e1 = b + 1 < nbins ? t.edges[b + 1] : 3 * n * n / 4 + 1;
+  const double s = bin_mode_sum<256>(partial, n_partial, nbins, 0, b, red);   // barriers inside
+  int cnt = 0;
+  for (int p = tid; p < (h + 1) * (h + 1); p += 256) {
+    const int i = p / (h + 1), j = p - i * (h + 1), r = i * i + j * j;
+    const int mult = ((i == 0 || i == h) ? 1 : 2) * ((j == 0 || j == h) ? 1 : 2);
+    cnt += mult * (lines_below(e1 - r, h) - lines_below(e0 - r, h));
   }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+  if ((tid & 63) == 0) atomicAdd(&s_cnt, cnt);
   __syncthreads();
-  for (int b = tid; b < nbins; b += blockDim.x) counts[b] = static_cast<double>(s_cnt[b]);
+  if (tid == 0) {
+    const double c = static_cast<double>(s_cnt);
+    pcdm[b] = c > 0.0 ? norm * s / c : 0.0;
+  }
 }
 
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
@@ -115,10 +149,8 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
   const int n_partial = fwd_x_partials(n);
   size_t off = 0;
   const size_t o_rho = off;     off = align256(off + M * sizeof(unsigned long long));
-  const size_t o_ca = off;      off = align256(off + MH * sizeof(float2));
   const size_t o_cb = off;      off = align256(off + MH * sizeof(float2));
   const size_t o_part = off;    off = align256(off + static_cast<size_t>(n_partial) * n_kbins * sizeof(double));
-  const size_t o_counts = off;  off = align256(off + n_kbins * sizeof(double));
   const size_t o_bins = off;    off = align256(off + (n2max + 1) * sizeof(uint16_t));
   const size_t o_tw = off;      off = align256(off + n * sizeof(float2));
   const size_t o_flags = off;   off = align256(off + sizeof(int));
@@ -131,10 +163,8 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
   if (rc) return rc;
   unsigned char* s = static_cast<unsigned char*>(base);
   auto* rho = reinterpret_cast<unsigned long long*>(s + o_rho);
-  auto* ca = reinterpret_cast<float2*>(s + o_ca);
   auto* cb = reinterpret_cast<float2*>(s + o_cb);
   auto* part = reinterpret_cast<double*>(s + o_part);
-  auto* counts = reinterpret_cast<double*>(s + o_counts);
   auto* bins = reinterpret_cast<uint16_t*>(s + o_bins);
   auto* tw = reinterpret_cast<float2*>(s + o_tw);
   auto* flags = reinterpret_cast<int*>(s + o_flags);
@@ -150,18 +180,22 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
     t.tw[m] = make_float2(static_cast<float>(std::cos(ph)), static_cast<float>(std::sin(ph)));
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(static_setup_kernel, dim3(1), dim3(1024), 0, st, t, n, n_kbins, n2max, bins,
-                     tw, counts);
+  const int64_t pairs = M / 2;                  // the density as pairs of 64-bit nodes
+  const int64_t threads = std::max<int64_t>(pairs, n2max + 1);
+  hipLaunchKernelGGL(static_setup_kernel, dim3(static_cast<unsigned>((threads + 511) / 512)),
+                     dim3(512), 0, st, t, n, n_kbins, n2max, bins, tw,
+                     reinterpret_cast<ulonglong2*>(rho), pairs);
   hipError_t e = hipGetLastError();
   const double scale = static_cast<double>(M) / static_cast<double>(n_particles) / kFixScale;
   const double norm = std::pow(box_size, 3) / (static_cast<double>(M) * M);
-  e = e ? e : launch_fill_zero(rho, M * static_cast<int64_t>(sizeof(unsigned long long)), st);
-  e = e ? e : launch_fill_zero(flags, sizeof(int), st);
   e = e ? e : launch_deposit(pos, rho, n_particles, 1, n, n / box_size, flags, 4, 256, st);
-  e = e ? e : launch_fwd_z(n, rho, nullptr, nullptr, nullptr, 0, ca, tw, scale, 1, st);
-  e = e ? e : launch_fwd_y(n, ca, cb, tw, 1, st);
+  e = e ? e : launch_fwd_zy(n, rho, nullptr, nullptr, nullptr, 0, cb, tw, scale, 1, st);
   e = e ? e : launch_fwd_x_bin(n, cb, tw, bins, part, n_kbins, 1, st);
-  e = e ? e : launch_bin_power(part, n_partial, counts, n_kbins, norm, 1, p_cdm, st);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(static_power_kernel, dim3(n_kbins), dim3(256), 0, st, t, n, n_kbins, part,
+                       n_partial, norm, p_cdm);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess)
     return set_error(PM_NU_EHIP, "no-allocation spectrum launch failed: %s", hipGetErrorString(e));
   return PM_NU_OK;
