@@ -987,6 +987,14 @@ hipError_t launch_tiled(const float* pos, unsigned long long* rho, int64_t np, i
   return hipGetLastError();
 }
 
+// Mode 4 takes chunks of 512 particles on 256 threads where the 4096-particle chunks would
+// leave the chip idle, or a chunk would be most of a small mesh (boxes up to 32^3, whose tile
+// of a 16^3 block plus its halo is the mesh again for every chunk). A tile of 3328 nodes
+// (27 KB) holds an 8^3 block with a halo of three nodes a side. Deposit alone, us, 4096 -> 512
+// particles a chunk, Morton order: one 32^3 box 10.0 -> 5.0 (8 workgroups -> 64), one 64^3 box
+// 11.9 -> 9.4, 16 and 256 boxes of 32^3 28.9 -> 13.0 and 234 -> 123. From 512 chunks of 4096
+// on the larger chunk has fewer atomics to flush and wins (128^3: 30.5 against 36.1).
+constexpr int64_t kSmallDeposit = 512;
 // mode 0: one thread per particle, global atomics (`block` threads per workgroup);
 // modes 1-5: LDS-privatised chunks of 1024 / 2048 / 4096 particles with 256 threads, 4096
 // with 512 threads, 8192 with 1024 threads.
@@ -996,7 +1004,10 @@ hipError_t launch_deposit(const float* pos, unsigned long long* rho, int64_t np,
     case 1: return launch_tiled<1024, 3328, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
     case 2: return launch_tiled<2048, 5120, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
     case 3: return launch_tiled<4096, 9216, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
-    case 4: return launch_tiled<4096, 9216, 512>(pos, rho, np, nbox, n, inv_cell, flags, s);
+    case 4:
+      if (n <= 32 || (np + 4095) / 4096 * nbox < kSmallDeposit)
+        return launch_tiled<512, 3328, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
+      return launch_tiled<4096, 9216, 512>(pos, rho, np, nbox, n, inv_cell, flags, s);
     case 5: return launch_tiled<8192, 18432, 1024>(pos, rho, np, nbox, n, inv_cell, flags, s);
     default:
       hipLaunchKernelGGL(deposit_kernel, dim3(grid_blocks(np * nbox, block, 1)), dim3(block), 0,
