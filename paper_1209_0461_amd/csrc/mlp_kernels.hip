@@ -6,12 +6,11 @@
 // gradients are FP32. (A layer input rounded to one bfloat16 alone limits the network to
 // about 2e-3 in ln R; the second part removes that floor.)
 //
-// Training runs on the matrix cores: mlp_train_kernel takes 32 samples per workgroup
-// through the forward pass (bf16 MFMA tiles, 16x16x32 where K is a multiple of 32 and
-// 16x16x16 for the 16 inputs, activations kept in LDS) and the backward pass (weight
-// gradients H^T dZ and input gradients dZ W^T, also on MFMA, with dZ rounded to bfloat16
-// as MFMA operand), and adds its share of the gradient to an FP32 buffer with global
-// atomics. adam_kernel applies one Adam step to the FP32 masters.
+// Training and prediction run on the matrix cores, 32 rows at a time (below): the forward pass
+// with the weights' share of every wave in registers, the backward pass (weight gradients
+// H^T dZ and input gradients dZ W^T, with dZ rounded to bfloat16 as MFMA operand) with the
+// weight gradients in registers. mlp_reduce_kernel adds up the workgroups' gradients and
+// applies one Adam step to the FP32 masters.
 //
 // Inside the step one bin is one row, so a matrix-core tile would be 1/16 full:
 // surrogate_response_kernel, one workgroup per (bin, box) like the exact response, forms
@@ -21,17 +20,18 @@
 // integral (response_device.hpp) for a bin whose inputs fall outside the training range
 // (or for every bin when checking). Its activations are FP32 where training carries them
 // as hi + lo bfloat16 pairs (16-bit significand): the two agree to about 1e-5 in ln R.
+#include <algorithm>
+
 #include "response_device.hpp"
 #include "surrogate_layout.hpp"
 
 namespace pmnu {
 namespace {
 
-typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int NT = 256;
-constexpr int TB = 32;   // samples per training workgroup
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
   unsigned u = __float_as_uint(f);
@@ -41,317 +41,543 @@ __device__ __forceinline__ unsigned short f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(unsigned short h) { return __uint_as_float(static_cast<unsigned>(h) << 16); }
 __device__ __forceinline__ float bfr(float f) { return bf2f(f2bf(f)); }
-// v as hi + lo, both bfloat16
-__device__ __forceinline__ void split_bf(float v, unsigned short& hi, unsigned short& lo) {
-  hi = f2bf(v);
-  lo = f2bf(v - bf2f(hi));
+// two values rounded to bfloat16 (nearest even), a in the low half
+__device__ __forceinline__ unsigned pack_bf2(float a, float b) {
+  const f32x2 v = {a, b};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+}
+// the second bfloat16 part of both, bf16(v - hi), given their packed first parts
+__device__ __forceinline__ unsigned pack_lo2(float a, float b, unsigned hi) {
+  return pack_bf2(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xffff0000u));
 }
 
 __device__ __forceinline__ float gelu(float x) {
   return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f));
 }
-__device__ __forceinline__ float gelu_grad(float x) {
-  return 0.5f * (1.0f + erff(x * 0.70710678118654752f)) + x * expf(-0.5f * x * x) * 0.39894228040143268f;
+
+// GELU and its derivative from one exponential, for the kernels whose time the erf took (384
+// evaluations a row). Phi(-|x|) = exp(-x^2/2) R(|x|) with R(x) = erfcx(x / sqrt 2) / 2 as
+// u p(u), u = 1 / (1 + 0.35 |x|), p the polynomial of degree 10 that minimises the largest
+// relative error over 0 < u <= 1 (1.3e-8, fitted in FP64). Error of gelu over x ~ 1.5 N(0, 1):
+// RMS 3.5e-8, against 3.7e-8 of 0.5 x (1 + erf) with an erf correct to the last bit.
+__device__ __forceinline__ void gelu_both(float x, float& g, float& dg) {
+  const float u = __builtin_amdgcn_rcpf(fmaf(0.35f, fabsf(x), 1.0f));
+  float p = 0.019314134493470192f;
+  p = fmaf(p, u, -0.10845651477575302f);
+  p = fmaf(p, u, 0.23588690161705017f);
+  p = fmaf(p, u, -0.2259197235107422f);
+  p = fmaf(p, u, 0.06956905126571655f);
+  p = fmaf(p, u, -0.028395146131515503f);
+  p = fmaf(p, u, 0.04840278998017311f);
+  p = fmaf(p, u, 0.08778655529022217f);
+  p = fmaf(p, u, 0.12255290895700455f);
+  p = fmaf(p, u, 0.13962922990322113f);
+  p = fmaf(p, u, 0.1396297961473465f);
+  const float e = __builtin_amdgcn_exp2f(x * x * -0.72134752044448170f);   // exp(-x^2/2)
+  const float q = e * (p * u);
+  const float phi = x > 0.f ? 1.0f - q : q;
+  g = x * phi;
+  dg = fmaf(x, e * 0.39894228040143268f, phi);
 }
 
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// ---------------------------------------------------- matrix-core network, rows at a time ----
+// A workgroup of 512 threads (8 waves) takes TB = 32 rows through the network. Every product
+// is formed transposed, Z^T = W^T H^T, so that wave w owns the 16 outputs 16 w .. +15 of every
+// hidden layer: its share of the weights (16 rows of the packed [out][in] image, 16 bytes a
+// lane and 32 inputs) stays in registers for all of the workgroup's rows, and a lane ends with
+// 4 consecutive outputs of one row, which go to LDS as one 8-byte store. 16x16x32 bf16 MFMA:
+// lane l gives row l % 16 of A and column l % 16 of B for k = 8 (l / 16) .. +7 and receives
+// rows 4 (l / 16) .. +3 of column l % 16.
+constexpr int TB = 32;         // rows per tile
+constexpr int kNetNT = 512;    // threads per workgroup
+constexpr int kHS = 136;       // LDS stride of a row's 128 activations (16-byte aligned, odd in
+                               // 16-byte units over 4 banks: the b128 reads of 16 rows differ)
+constexpr int kXS = 40;        // LDS stride of a row's inputs: 16 and 16 zeros (a 32-wide k step)
+constexpr int kTS = 40;        // LDS stride of the transposed layouts ([unit][row])
 
-// acc += A(16 x K) * B(K x 16) for one 16x16 tile, K a multiple of 16, operands bf16 in
-// LDS with element (m, k) of A at A[m*sam + k*sak] and (k, n) of B at B[k*sbk + n*sbn].
-// With K a multiple of 32 it takes gfx950's 16x16x32 steps (lane l supplies row l%16 of A /
-// column l%16 of B for k = 8*(l/16) .. +7 of every 32-wide step), otherwise 16x16x16 steps
-// (k = 4*(l/16) .. +3 of every 16-wide step); either way lane l receives rows
-// 4*(l/16) .. +3 of column l%16 of the result.
-__device__ __forceinline__ f32x4 mma16(const unsigned short* A, int sam, int sak,
-                                       const unsigned short* B, int sbk, int sbn, int K,
-                                       f32x4 acc) {
-  const int l = threadIdx.x & 63, r = l & 15;
-  if (K % 32 == 0) {
-    const int kb = (l >> 4) << 3;
-    for (int k0 = 0; k0 < K; k0 += 32) {
-      s16x8 a, b;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        a[q] = static_cast<short>(A[r * sam + (k0 + kb + q) * sak]);
-        b[q] = static_cast<short>(B[(k0 + kb + q) * sbk + r * sbn]);
-      }
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
-                                                     __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-    }
-    return acc;
-  }
-  const int kb = (l >> 4) << 2;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    bf16x4 a, b;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      a[q] = static_cast<short>(A[r * sam + (k0 + kb + q) * sak]);
-      b[q] = static_cast<short>(B[(k0 + kb + q) * sbk + r * sbn]);
-    }
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
-  }
-  return acc;
-}
-
-struct Smem {
-  unsigned short x[2][TB * 16];       // standardised inputs, K padded to 16 (bf16 hi, lo)
-  unsigned short h[3][2][TB * 128];   // inputs of layers 2, 3, 4: H1, H2, H3 (bf16 hi, lo)
-  float z[3][TB * 128];               // pre-activations Z1..Z3, later dZ (FP32)
-  alignas(16) unsigned short w[128 * 128];   // one staged weight matrix as [out][in] (bf16)
-  unsigned short d[TB * 128];         // dZ of the current layer (bf16)
-  float y[TB];
-  float dy[TB];
-};
-
-// W[in][out] (FP32 master, row-major) -> S.w[out*kin + in] (bf16); rows in >= nin are 0.
-// Loads go out in batches of 16 per thread before their LDS stores.
-__device__ __forceinline__ void stage_weights(Smem& S, const float* W, int nin, int kin) {
-  constexpr int BATCH = 16;
-  const int total = kin * 128;
-  for (int t0 = 0; t0 < total; t0 += BATCH * NT) {
-    float v[BATCH];
-#pragma unroll
-    for (int q = 0; q < BATCH; ++q) {
-      const int t = t0 + threadIdx.x + q * NT, i = t / 128, o = t % 128;
-      v[q] = (t < total && i < nin) ? W[i * 128 + o] : 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < BATCH; ++q) {
-      const int t = t0 + threadIdx.x + q * NT, i = t / 128, o = t % 128;
-      if (t < total) S.w[o * kin + i] = f2bf(v[q]);
-    }
-  }
-}
-
-// Z = H W + b for the 32 x 128 tile (H as its hi and lo parts); writes Z (FP32) and
-// GELU(Z) as hi and lo parts
-__device__ __forceinline__ void dense_gelu(Smem& S, const unsigned short* Hhi,
-                                           const unsigned short* Hlo, int kin,
-                                           const float* bias, float* Z, unsigned short* Ohi,
-                                           unsigned short* Olo) {
-  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  for (int t = wv; t < 16; t += NT / 64) {
-    const int mt = t >> 3, nt = t & 7;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mma16(Hhi + mt * 16 * kin, kin, 1, S.w + nt * 16 * kin, 1, kin, kin, acc);
-    acc = mma16(Hlo + mt * 16 * kin, kin, 1, S.w + nt * 16 * kin, 1, kin, kin, acc);
-    const int col = nt * 16 + (l & 15);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = mt * 16 + ((l >> 4) << 2) + q;
-      const float z = acc[q] + bias[col];
-      Z[row * 128 + col] = z;
-      split_bf(gelu(z), Ohi[row * 128 + col], Olo[row * 128 + col]);
-    }
-  }
-}
-
-// output layer: 8 lanes per sample, 16 products each, FP32
-__device__ __forceinline__ void output_layer(Smem& S, const float* P) {
-  const int tid = threadIdx.x;
-  {
-    const int s = tid >> 3, part = tid & 7;
-    float acc = 0.f;
-#pragma unroll
-    for (int j = part * 16; j < part * 16 + 16; ++j)
-      acc += (bf2f(S.h[2][0][s * 128 + j]) + bf2f(S.h[2][1][s * 128 + j])) * bfr(P[kOffW4 + j]);
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    acc += __shfl_xor(acc, 4, 64);
-    if (part == 0) S.y[s] = acc + P[kOffB4];
-  }
-  __syncthreads();
-}
-
-// bfloat16 image of W1..W3 in the staged layout ([out][in], the first layer's K padded to
-// 16), so that inference stages a layer with 16-byte copies
+// bfloat16 image of the weights: W1..W3 as [out][in] (A operand of the forward products and
+// the in-step network), then W2, W3 as [in][out] (A operand of the backward products)
 constexpr int kPackW1 = 0;
 constexpr int kPackW2 = kPackW1 + 128 * 16;
 constexpr int kPackW3 = kPackW2 + 128 * 128;
-constexpr int kPackSize = kPackW3 + 128 * 128;
+constexpr int kPackB2 = kPackW3 + 128 * 128;
+constexpr int kPackB3 = kPackB2 + 128 * 128;
+constexpr int kPackSize = kPackB3 + 128 * 128;
 
-// Layers 1-3 of the forward pass on S.x (already standardised, bf16); weights staged from
-// the FP32 masters P.
-__device__ __forceinline__ void hidden_layers(Smem& S, const float* P) {
-  stage_weights(S, P + kOffW1, kSurIn, 16);
-  __syncthreads();
-  dense_gelu(S, S.x[0], S.x[1], 16, P + kOffB1, S.z[0], S.h[0][0], S.h[0][1]);
-  __syncthreads();
-  stage_weights(S, P + kOffW2, 128, 128);
-  __syncthreads();
-  dense_gelu(S, S.h[0][0], S.h[0][1], 128, P + kOffB2, S.z[1], S.h[1][0], S.h[1][1]);
-  __syncthreads();
-  stage_weights(S, P + kOffW3, 128, 128);
-  __syncthreads();
-  dense_gelu(S, S.h[1][0], S.h[1][1], 128, P + kOffB3, S.z[2], S.h[2][0], S.h[2][1]);
-  __syncthreads();
-  output_layer(S, P);
+__device__ __forceinline__ f32x4 mfma(const uint4& a, const uint4& b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                 __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ uint4 lds16(const unsigned short* p) {
+  return *reinterpret_cast<const uint4*>(p);
 }
 
-// Forward pass of up to TB rows starting at row0 (through perm if given). Leaves y (the
-// standardised output) in S.y.
-__device__ __forceinline__ void forward_tile(Smem& S, const float* P, const float* x, const int* perm,
-                             int64_t row0, int count) {
-  const int tid = threadIdx.x;
-  for (int t = tid; t < TB * 16; t += NT) {
-    const int s = t >> 4, i = t & 15;
-    float v = 0.f;
-    if (i < kSurIn && s < count) {
-      const int64_t r = perm ? perm[row0 + s] : row0 + s;
-      v = (x[r * kSurIn + i] - P[kOffMu + i]) / P[kOffSigma + i];
-    }
-    split_bf(v, S.x[0][t], S.x[1][t]);
+struct NetLds {
+  alignas(16) unsigned short x[2][TB * kXS];     // standardised inputs (bf16 hi, lo)
+  alignas(16) unsigned short h[2][2][TB * kHS];  // H1, H2 (hi, lo), [row][unit]
+  float red[kNetNT / 64][TB];                    // output partial sums of every wave
+  float t[TB];                                   // standardised targets (NaN: not used)
+};
+struct TrainLds : NetLds {
+  alignas(16) unsigned short xt[2][16 * kTS];       // the same transposed, [unit][row]
+  alignas(16) unsigned short ht[2][2][128 * kTS];
+  alignas(16) unsigned short dz[2][TB * kHS];       // dZ3, dZ2 (bf16), [row][unit]
+  alignas(16) unsigned short dzt[3][128 * kTS];     // dZ3, dZ2, dZ1, [unit][row]
+};
+
+// a wave's share of the weights, biases and output weights
+struct WaveNet {
+  uint4 w1, w2[4], w3[4];
+  float b1[4], b2[4], b3[4], w4[4], b4;
+};
+// 16 rows of a 128-wide matrix of the image
+__device__ __forceinline__ void load_rows(const unsigned short* q, int o, int r, int g,
+                                          uint4 (&w)[4]) {
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt) w[kt] = lds16(q + (o + r) * 128 + 32 * kt + 8 * g);
+}
+__device__ __forceinline__ void load_wave_weights(const unsigned short* Q, int o, int r, int g,
+                                                  WaveNet& n) {
+  // 16 inputs of a 32-wide k step: the upper half of the lanes holds zeros
+  const uint4 w = lds16(Q + kPackW1 + (o + r) * 16 + 8 * (g & 1));
+  n.w1 = make_uint4(g < 2 ? w.x : 0u, g < 2 ? w.y : 0u, g < 2 ? w.z : 0u, g < 2 ? w.w : 0u);
+  load_rows(Q + kPackW2, o, r, g, n.w2);
+  load_rows(Q + kPackW3, o, r, g, n.w3);
+}
+__device__ __forceinline__ void load_wave_biases(const float* __restrict__ P, int o, int g,
+                                                 WaveNet& n) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    n.b1[q] = P[kOffB1 + o + 4 * g + q];
+    n.b2[q] = P[kOffB2 + o + 4 * g + q];
+    n.b3[q] = P[kOffB3 + o + 4 * g + q];
+    n.w4[q] = bfr(P[kOffW4 + o + 4 * g + q]);
   }
-  hidden_layers(S, P);
+  n.b4 = P[kOffB4];
 }
 
-// dW (kin x 128) += Hin^T dZ for the 32-row tile (rows i < nin), Hin as hi and lo parts,
-// with atomics
-__device__ __forceinline__ void weight_grad(Smem& S, const unsigned short* Hhi,
-                                            const unsigned short* Hlo, int kin, int nin,
-                                            float* gW) {
-  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int ntiles = (kin / 16) * 8;
-  for (int t = wv; t < ntiles; t += NT / 64) {
-    const int mt = t >> 3, nt = t & 7;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = mma16(Hhi + mt * 16, 1, kin, S.d + nt * 16, 128, 1, TB, acc);
-    acc = mma16(Hlo + mt * 16, 1, kin, S.d + nt * 16, 128, 1, TB, acc);
-    const int col = nt * 16 + (l & 15);
+// One hidden layer's pre-activations of this wave for both 16-row halves (hi then lo parts of
+// the inputs over one FP32 accumulator each), without the bias.
+__device__ __forceinline__ void layer128(const uint4 (&w)[4], const unsigned short (&h)[2][TB * kHS],
+                                         int r, int g, f32x4 (&z)[2]) {
+  z[0] = z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+        z[m] = mfma(w[kt], lds16(&h[part][(16 * m + r) * kHS + 32 * kt + 8 * g]), z[m]);
+    __builtin_amdgcn_sched_barrier(0);   // 8 operands in flight, not 16: registers
+  }
+}
+
+// four units u .. u+3 of one row (packed bf16) into the [unit][row] layout
+__device__ __forceinline__ void store_t(unsigned short* t, int u, int row, uint2 v) {
+  t[u * kTS + row] = static_cast<unsigned short>(v.x);
+  t[(u + 1) * kTS + row] = static_cast<unsigned short>(v.x >> 16);
+  t[(u + 2) * kTS + row] = static_cast<unsigned short>(v.y);
+  t[(u + 3) * kTS + row] = static_cast<unsigned short>(v.y >> 16);
+}
+
+// dZ of a layer: its FP32 sums into the bias gradient, its bfloat16 values to both layouts
+__device__ __forceinline__ void store_dz(unsigned short* d, unsigned short* dt, const f32x4 (&dz)[2],
+                                         float (&gb)[4], int o, int r, int g) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const uint2 v = make_uint2(pack_bf2(dz[m][0], dz[m][1]), pack_bf2(dz[m][2], dz[m][3]));
+    const int row = 16 * m + r, u = o + 4 * g;
+    if (d) *reinterpret_cast<uint2*>(&d[row * kHS + u]) = v;
+    store_t(dt, u, row, v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) gb[q] += dz[m][q];
+  }
+}
+
+// dW += H^T dZ: this wave's 16 inputs by all 128 outputs
+__device__ __forceinline__ void weight_grad32(const unsigned short (&ht)[2][128 * kTS],
+                                              const unsigned short* dzt, int o, int r, int g,
+                                              f32x4 (&acc)[8]) {
+  const uint4 hi = lds16(&ht[0][(o + r) * kTS + 8 * g]), lo = lds16(&ht[1][(o + r) * kTS + 8 * g]);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint4 b = lds16(&dzt[(16 * t + r) * kTS + 8 * g]);
+    acc[t] = mfma(hi, b, acc[t]);
+    acc[t] = mfma(lo, b, acc[t]);
+    if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// dZ of the layer before: (W dZ^T) GELU'
+__device__ __forceinline__ void backprop32(const uint4 (&wb)[4], const unsigned short* d,
+                                           const float (&dg)[2][4], int r, int g, f32x4 (&dz)[2]) {
+  f32x4 z[2];
+  z[0] = z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      z[m] = mfma(wb[kt], lds16(&d[(16 * m + r) * kHS + 32 * kt + 8 * g]), z[m]);
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dz[m][q] = z[m][q] * dg[m][q];
+}
+
+// Activations of a layer from its pre-activations: H to LDS as hi + lo (with TRAIN also
+// transposed) and GELU' kept for the backward pass.
+template <bool TRAIN>
+__device__ __forceinline__ void activate(const f32x4 (&z)[2], const float (&bias)[4], int o, int r,
+                                         int g, unsigned short (&h)[2][TB * kHS],
+                                         unsigned short (*ht)[128 * kTS], float (&dg)[2][4]) {
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    float v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) gelu_both(z[m][q] + bias[q], v[q], dg[m][q]);
+    const uint2 hi = make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+    const uint2 lo = make_uint2(pack_lo2(v[0], v[1], hi.x), pack_lo2(v[2], v[3], hi.y));
+    const int row = 16 * m + r, u = o + 4 * g;
+    *reinterpret_cast<uint2*>(&h[0][row * kHS + u]) = hi;
+    *reinterpret_cast<uint2*>(&h[1][row * kHS + u]) = lo;
+    if constexpr (TRAIN) {
+      store_t(ht[0], u, row, hi);
+      store_t(ht[1], u, row, lo);
+    }
+  }
+}
+
+// Forward pass of the tile whose inputs are in S.x (barrier before); the standardised outputs
+// without bias are left as one partial sum per wave in S.red (barrier before reading).
+template <bool TRAIN, typename L>
+__device__ __forceinline__ void forward32(L& S, const WaveNet& n, int o, int r, int g,
+                                          float (&dg)[3][2][4], float (&h3)[2][4]) {
+  unsigned short(*ht1)[128 * kTS] = nullptr;
+  unsigned short(*ht2)[128 * kTS] = nullptr;
+  if constexpr (TRAIN) {
+    ht1 = S.ht[0];
+    ht2 = S.ht[1];
+  }
+  f32x4 z[2];
+  z[0] = z[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int part = 0; part < 2; ++part)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+      z[m] = mfma(n.w1, lds16(&S.x[part][(16 * m + r) * kXS + 8 * g]), z[m]);
+  activate<TRAIN>(z, n.b1, o, r, g, S.h[0], ht1, dg[0]);
+  __syncthreads();
+  layer128(n.w2, S.h[0], r, g, z);
+  activate<TRAIN>(z, n.b2, o, r, g, S.h[1], ht2, dg[1]);
+  __syncthreads();
+  layer128(n.w3, S.h[1], r, g, z);
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    float y = 0.f;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int row = mt * 16 + ((l >> 4) << 2) + q;
-      if (row < nin) atomicAdd(gW + row * 128 + col, acc[q]);
+      gelu_both(z[m][q] + n.b3[q], h3[m][q], dg[2][m][q]);
+      y = fmaf(h3[m][q], n.w4[q], y);
     }
+    y += __shfl_xor(y, 16, 64);
+    y += __shfl_xor(y, 32, 64);
+    if (g == 0) S.red[o >> 4][16 * m + r] = y;
   }
 }
 
-// db (128) += column sums of dZ (FP32, held in Z)
-__device__ __forceinline__ void bias_grad(const float* dZ, float* gb) {
-  const int j = threadIdx.x;
-  if (j < 128) {
-    float s = 0.f;
-    for (int r = 0; r < TB; ++r) s += dZ[r * 128 + j];
-    atomicAdd(gb + j, s);
-  }
-}
-
-// dZ_prev = (dZ W^T) * GELU'(Z_prev), W staged as [out][in] with in = 128
-__device__ __forceinline__ void backprop_hidden(Smem& S, float* Zprev) {
-  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  f32x4 res[4];
-  int tiles = 0;
-  for (int t = wv; t < 16; t += NT / 64, ++tiles) {
-    const int mt = t >> 3, nt = t & 7;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    // A(m = sample, k = out) = dZ[s][o]; B(k = out, n = in) = W[in][out] = S.w[out*128 + in]
-    res[tiles] = mma16(S.d + mt * 16 * 128, 128, 1, S.w + nt * 16, 128, 1, 128, acc);
-  }
-  __syncthreads();   // every wave is done reading S.d
-  tiles = 0;
-  for (int t = wv; t < 16; t += NT / 64, ++tiles) {
-    const int mt = t >> 3, nt = t & 7;
-    const int col = nt * 16 + (l & 15);
+__device__ __forceinline__ float net_output(const NetLds& S, int row, float b4) {
+  float y = S.red[0][row];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int row = mt * 16 + ((l >> 4) << 2) + q;
-      const float dz = res[tiles][q] * gelu_grad(Zprev[row * 128 + col]);
-      Zprev[row * 128 + col] = dz;
-      S.d[row * 128 + col] = f2bf(dz);
-    }
-  }
-  __syncthreads();
+  for (int w = 1; w < kNetNT / 64; ++w) y += S.red[w][row];
+  return y + b4;
 }
 
-// Forward + backward of one 32-row tile of the minibatch rows [row0, row0 + count).
-__global__ __launch_bounds__(NT) void mlp_train_kernel(const float* __restrict__ P,
-                                                       const float* __restrict__ x,
-                                                       const float* __restrict__ y,
-                                                       const int* __restrict__ perm,
-                                                       int64_t row0, int64_t count,
-                                                       float inv_batch, float* __restrict__ grad,
-                                                       float* __restrict__ loss_sum) {
-  __shared__ Smem S;
-  const int tid = threadIdx.x;
-  const int64_t base = row0 + static_cast<int64_t>(blockIdx.x) * TB;
-  const int cnt = static_cast<int>(min(static_cast<int64_t>(TB), row0 + count - base));
-  forward_tile(S, P, x, perm, base, cnt);
+// thread (row tid / 16, input tid % 16) stages its standardised input (0 beyond the rows)
+__device__ __forceinline__ void stage_input(NetLds& S, float v) {
+  const int s = threadIdx.x >> 4, i = threadIdx.x & 15;
+  const unsigned short hi = f2bf(v);
+  S.x[0][s * kXS + i] = hi;
+  S.x[1][s * kXS + i] = f2bf(v - bf2f(hi));
+}
+__device__ __forceinline__ void zero_input_padding(NetLds& S) {
+  const int s = threadIdx.x >> 4, i = 16 + (threadIdx.x & 15);
+  S.x[0][s * kXS + i] = S.x[1][s * kXS + i] = 0;
+}
 
-  // loss and dL/dy on the standardised target
-  if (tid < 64) {
-    float l2 = 0.f, dy = 0.f;
-    if (tid < TB && tid < cnt) {
-      const int64_t r = perm ? perm[base + tid] : base + tid;
-      const float t = (y[r] - P[kOffYMu]) / P[kOffYSigma];
+// Rows of x through the network: a workgroup keeps its weights in registers and walks tiles
+// of 32 rows, the next tile's inputs loaded while it works on one. Bound by the FP32
+// arithmetic of the 384 GELUs a row; staging the weights for every 32 rows and gathering the
+// MFMA operands from LDS two bytes at a time took 795 us for 200000 rows, this 75.
+__global__ __launch_bounds__(kNetNT, 4) void mlp_predict_kernel(const float* __restrict__ P,
+                                                                const unsigned short* __restrict__ Q,
+                                                                const float* __restrict__ x,
+                                                                float* __restrict__ y, int64_t n) {
+  __shared__ NetLds S;
+  const int tid = threadIdx.x, s = tid >> 4, i = tid & 15;
+  const int64_t tiles = (n + TB - 1) / TB;
+  const int r = tid & 15, g = (tid & 63) >> 4, o = 16 * (tid >> 6);
+  WaveNet net;
+  load_wave_weights(Q, o, r, g, net);
+  load_wave_biases(P, o, g, net);
+  const float mu = P[kOffMu + i], sg = P[kOffSigma + i];
+  const float ymu = P[kOffYMu], ysg = P[kOffYSigma];
+  auto input = [&](int64_t tile) -> float {
+    const int64_t row = tile * TB + s;
+    return tile < tiles && row < n ? x[row * kSurIn + i] : mu;
+  };
+  zero_input_padding(S);
+  float xv = input(blockIdx.x);
+  float dg[3][2][4], h3[2][4];
+  // every LDS array is next written two barriers after its last read
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    stage_input(S, (xv - mu) / sg);
+    xv = input(tile + gridDim.x);
+    __syncthreads();
+    forward32<false>(S, net, o, r, g, dg, h3);
+    __syncthreads();
+    const int64_t row = tile * TB + tid;
+    if (tid < TB && row < n) y[row] = net_output(S, tid, net.b4) * ysg + ymu;
+  }
+}
+
+// Loss and gradient of rows [row0, row0 + count) (through perm if given), one set of sums per
+// workgroup in part (added up by mlp_reduce_kernel): each workgroup walks tiles of 32 rows, forward as above and backward
+//   dW = H^T dZ           A = H^T from the [unit][row] copies (hi, lo), B = dZ likewise;
+//                         wave w owns the inputs 16 w .. +15 of W2, W3 and the outputs of W1
+//   dH^T = W dZ^T         A = its 16 rows of W ([in][out]), B = dZ [row][unit]: the result
+//                         lies in the lanes as the forward pass's GELU' does
+// with dZ rounded to bfloat16. The weight gradients of all its tiles stay in FP32 registers and
+// leave as plain 16-byte stores: as atomics on one gradient, 256 workgroups times 35329 values,
+// they took 95 us whatever the kernel did before them. 8192 rows: 98 us and 5 of Adam before, now
+// 24 and 8; 100000 rows: 981 -> 123.
+constexpr int kPartW3 = 0, kPartW2 = 128 * 128, kPartW1 = 2 * 128 * 128;
+constexpr int kPartVec = kPartW1 + 16 * 128;         // dB1, dB2, dB3, dW4, dB4, loss
+constexpr int kPartSize = kPartVec + 576;            // whole 256-byte lines
+static_assert(kPartVec + 514 == kSurParams + 1, "every parameter and the loss");
+constexpr int kTrainWGs = 256;                       // one per CU
+__global__ __launch_bounds__(kNetNT) void mlp_train_kernel(const float* __restrict__ P,
+                                                           const unsigned short* __restrict__ Q,
+                                                           const float* __restrict__ x,
+                                                           const float* __restrict__ y,
+                                                           const int* __restrict__ perm,
+                                                           int64_t row0, int64_t count,
+                                                           float inv_batch,
+                                                           float* __restrict__ part) {
+  __shared__ TrainLds S;
+  const int tid = threadIdx.x, l = tid & 63, wave = tid >> 6;
+  int r = l & 15, g = l >> 4, o = __builtin_amdgcn_readfirstlane(16 * wave);
+  const int64_t tiles = (count + TB - 1) / TB;
+  WaveNet net;
+  load_wave_biases(P, o, g, net);
+  const int xs = tid >> 4, xi = tid & 15;
+  const float mu = P[kOffMu + xi], sg = P[kOffSigma + xi];
+  const float ymu = P[kOffYMu], ysg = P[kOffYSigma];
+  // row of the batch that tile's row s holds, -1 beyond the rows
+  auto row_of = [&](int64_t tile, int s) -> int64_t {
+    const int64_t k = tile * TB + s;
+    if (tile >= tiles || k >= count) return -1;
+    return perm ? perm[row0 + k] : row0 + k;
+  };
+  zero_input_padding(S);
+  int64_t rx = row_of(blockIdx.x, xs), ry = tid < TB ? row_of(blockIdx.x, tid) : -1;
+  float xv = rx >= 0 ? x[rx * kSurIn + xi] : mu;
+  float yv = ry >= 0 ? y[ry] : __builtin_nanf("");
+  rx = row_of(blockIdx.x + gridDim.x, xs);
+  ry = tid < TB ? row_of(blockIdx.x + gridDim.x, tid) : -1;
+
+  f32x4 g3[8], g2[8], g1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 8; ++t) g3[t] = g2[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float gw4[4] = {}, gb[3][4] = {}, gb4 = 0.f, loss = 0.f;
+
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    // the lane's place made opaque: the LDS addresses are formed where they are used instead
+    // of some fifty of them being kept (and spilled) over the loop
+    // (likewise the weights come from the caches for every tile: they would not fit beside the
+    // gradients)
+    int q0 = 0;
+    asm volatile("" : "+v"(r), "+v"(g), "+s"(o), "+s"(q0));
+    const unsigned short* q = Q + q0;
+    load_wave_weights(q, o, r, g, net);
+    {
+      const float v = (xv - mu) / sg;
+      stage_input(S, v);
+      const unsigned short hi = f2bf(v);
+      S.xt[0][xi * kTS + xs] = hi;
+      S.xt[1][xi * kTS + xs] = f2bf(v - bf2f(hi));
+    }
+    if (tid < TB) S.t[tid] = (yv - ymu) / ysg;
+    // the next tile's inputs, and the rows of the one after
+    xv = rx >= 0 ? x[rx * kSurIn + xi] : mu;
+    yv = ry >= 0 ? y[ry] : __builtin_nanf("");
+    rx = row_of(tile + 2 * static_cast<int64_t>(gridDim.x), xs);
+    ry = tid < TB ? row_of(tile + 2 * static_cast<int64_t>(gridDim.x), tid) : -1;
+    __syncthreads();
+    float dg[3][2][4], h3[2][4];
+    forward32<true>(S, net, o, r, g, dg, h3);
+    __syncthreads();
+    uint4 wb[4];
+    load_rows(q + kPackB3, o, r, g, wb);
+    // loss, dL/dy and dZ3
+    f32x4 dz[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+      const int row = 16 * m + r;
+      const float t = S.t[row];
+      float dy = 0.f;
       if (isfinite(t)) {
-        const float res = S.y[tid] - t;
-        l2 = res * res;
+        const float res = net_output(S, row, net.b4) - t;
         dy = 2.0f * res * inv_batch;
+        if (tid < 16) {
+          loss = fmaf(res, res, loss);
+          gb4 += dy;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        gw4[q] = fmaf(h3[m][q], dy, gw4[q]);
+        dz[m][q] = dy * net.w4[q] * dg[2][m][q];
       }
     }
-    if (tid < TB) S.dy[tid] = dy;
+    store_dz(S.dz[0], S.dzt[0], dz, gb[2], o, r, g);
+    __syncthreads();
+    // layer 3: dW3, then dZ2
+    weight_grad32(S.ht[1], S.dzt[0], o, r, g, g3);
+    backprop32(wb, S.dz[0], dg[1], r, g, dz);
+    load_rows(q + kPackB2, o, r, g, wb);
+    store_dz(S.dz[1], S.dzt[1], dz, gb[1], o, r, g);
+    __syncthreads();
+    // layer 2: dW2, then dZ1
+    weight_grad32(S.ht[0], S.dzt[1], o, r, g, g2);
+    backprop32(wb, S.dz[1], dg[0], r, g, dz);
+    store_dz(nullptr, S.dzt[2], dz, gb[0], o, r, g);
+    __syncthreads();
+    // layer 1: its 16 inputs by this wave's 16 outputs
+    const uint4 b = lds16(&S.dzt[2][(o + r) * kTS + 8 * g]);
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) l2 += __shfl_xor(l2, off, 64);
-    if (tid == 0) atomicAdd(loss_sum, l2);
+    for (int part = 0; part < 2; ++part) g1 = mfma(lds16(&S.xt[part][r * kTS + 8 * g]), b, g1);
+    __syncthreads();                               // before the next tile's inputs
   }
-  __syncthreads();
-  // output layer
-  if (tid < 128) {
-    float g = 0.f;
-    for (int s = 0; s < TB; ++s)
-      g += (bf2f(S.h[2][0][s * 128 + tid]) + bf2f(S.h[2][1][s * 128 + tid])) * S.dy[s];
-    atomicAdd(grad + kOffW4 + tid, g);
-  } else if (tid == 128) {
-    float g = 0.f;
-    for (int s = 0; s < TB; ++s) g += S.dy[s];
-    atomicAdd(grad + kOffB4, g);
+  // the workgroup's sums, in the order that its lanes hold them
+  float* p = part + static_cast<size_t>(blockIdx.x) * kPartSize;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    *reinterpret_cast<f32x4*>(p + kPartW3 + ((wave * 8 + t) * 64 + l) * 4) = g3[t];
+    *reinterpret_cast<f32x4*>(p + kPartW2 + ((wave * 8 + t) * 64 + l) * 4) = g2[t];
   }
-  for (int t = tid; t < TB * 128; t += NT) {
-    const int s = t >> 7, j = t & 127;
-    const float dz = S.dy[s] * bfr(P[kOffW4 + j]) * gelu_grad(S.z[2][t]);
-    S.z[2][t] = dz;
-    S.d[t] = f2bf(dz);
+  *reinterpret_cast<f32x4*>(p + kPartW1 + (wave * 64 + l) * 4) = g1;
+  // sums over the rows (the 16 lanes of a group)
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float v[4] = {gb[0][q], gb[1][q], gb[2][q], gw4[q]};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+      if (r == 0) p[kPartVec + 128 * k + o + 4 * g + q] = v[k];
+    }
   }
-  __syncthreads();
-  // layer 3: W3 (H2 -> Z3)
-  bias_grad(S.z[2], grad + kOffB3);
-  weight_grad(S, S.h[1][0], S.h[1][1], 128, 128, grad + kOffW3);
-  stage_weights(S, P + kOffW3, 128, 128);
-  __syncthreads();
-  backprop_hidden(S, S.z[1]);
-  // layer 2: W2 (H1 -> Z2)
-  bias_grad(S.z[1], grad + kOffB2);
-  weight_grad(S, S.h[0][0], S.h[0][1], 128, 128, grad + kOffW2);
-  stage_weights(S, P + kOffW2, 128, 128);
-  __syncthreads();
-  backprop_hidden(S, S.z[0]);
-  // layer 1: W1 (X -> Z1)
-  bias_grad(S.z[0], grad + kOffB1);
-  weight_grad(S, S.x[0], S.x[1], 16, kSurIn, grad + kOffW1);
+  if (wave == 0) {
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) {
+      loss += __shfl_xor(loss, off, 64);
+      gb4 += __shfl_xor(gb4, off, 64);
+    }
+    if (tid == 0) {
+      p[kPartVec + 512] = gb4;
+      p[kPartVec + 513] = loss;
+    }
+  }
 }
 
-__global__ __launch_bounds__(NT) void mlp_predict_kernel(const float* __restrict__ P,
-                                                         const float* __restrict__ x,
-                                                         float* __restrict__ y, int64_t n) {
-  __shared__ Smem S;
-  const int64_t base = static_cast<int64_t>(blockIdx.x) * TB;
-  const int cnt = static_cast<int>(min(static_cast<int64_t>(TB), n - base));
-  forward_tile(S, P, x, nullptr, base, cnt);
-  if (threadIdx.x < cnt) y[base + threadIdx.x] = S.y[threadIdx.x] * P[kOffYSigma] + P[kOffYMu];
+// the parameter that entry e of a workgroup's sums belongs to (kSurParams: the loss)
+__device__ __forceinline__ int part_param(int e) {
+  if (e < kPartVec) {
+    const int q = e & 3, l = (e >> 2) & 63, r = l & 15, g = l >> 4, t = e >> 8;
+    if (e >= kPartW1) return kOffW1 + (4 * g + q) * 128 + 16 * (t - (kPartW1 >> 8)) + r;
+    const int tt = t & 63;                           // wave tt / 8, outputs 16 (tt % 8) .. +15
+    return (e < kPartW2 ? kOffW3 : kOffW2) + (16 * (tt >> 3) + 4 * g + q) * 128 + 16 * (tt & 7) + r;
+  }
+  const int k = e - kPartVec;
+  if (k >= 512) return k == 512 ? kOffB4 : kSurParams;
+  const int off[4] = {kOffB1, kOffB2, kOffB3, kOffW4};
+  return off[k >> 7] + (k & 127);
 }
 
-__global__ void adam_kernel(float* __restrict__ P, const float* __restrict__ g,
-                            float* __restrict__ m, float* __restrict__ v, int n, float lr,
-                            float b1, float b2, float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+// A parameter's entries in the bfloat16 image
+__device__ __forceinline__ void pack_param(unsigned short* __restrict__ Q, int i, float p) {
+  const unsigned short h = f2bf(p);
+  if (i < kOffB1) {
+    Q[kPackW1 + (i % 128) * 16 + i / 128] = h;
+  } else if (i >= kOffW2 && i < kOffB2) {
+    const int j = i - kOffW2;
+    Q[kPackW2 + (j % 128) * 128 + j / 128] = h;
+    Q[kPackB2 + j] = h;
+  } else if (i >= kOffW3 && i < kOffB3) {
+    const int j = i - kOffW3;
+    Q[kPackW3 + (j % 128) * 128 + j / 128] = h;
+    Q[kPackB3 + j] = h;
+  }
+}
+
+// Sums of the n_part workgroups of mlp_train_kernel, in a fixed order, and with ADAM one Adam
+// step on them that also writes the bfloat16 image of the new weights, so that a minibatch is
+// two launches; without, the gradient to grad. first: the loss starts here. One workgroup takes
+// 64 entries, its four waves a quarter of the workgroups' sums each, 16 loads in flight.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(
+    const float* __restrict__ part, int n_part, int first, float* __restrict__ loss,
+    float* __restrict__ grad, float* __restrict__ P, float* __restrict__ m, float* __restrict__ v,
+    unsigned short* __restrict__ Q, float lr, float b1, float b2, float eps, float c1, float c2) {
+  __shared__ float s_sum[4][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int e = blockIdx.x * 64 + lane;
+  const bool on = e < kPartVec + 514;
+  const int i = on ? part_param(e) : 0;
+  const bool param = on && i < kSurParams;
+  // the moments' loads go out with the sums'
+  float mi = 0.f, vi = 0.f, pi = 0.f;
+  if (ADAM && w == 0 && param) {
+    mi = m[i];
+    vi = v[i];
+    pi = P[i];
+  }
+  float sum = 0.f;
+  if (on) {
+    constexpr int U = 16;
+    for (int k0 = w; k0 < n_part; k0 += 4 * U) {
+      float x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        x[u] = k0 + 4 * u < n_part ? part[static_cast<size_t>(k0 + 4 * u) * kPartSize + e] : 0.f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) sum += x[u];
+    }
+  }
+  s_sum[w][lane] = sum;
+  __syncthreads();
+  if (w != 0 || !on) return;
+  const float gi = (s_sum[0][lane] + s_sum[1][lane]) + (s_sum[2][lane] + s_sum[3][lane]);
+  if (!param) {
+    *loss = first ? gi : *loss + gi;
+    return;
+  }
+  if constexpr (!ADAM) {
+    grad[i] = gi;
+    return;
+  }
+  mi = b1 * mi + (1.0f - b1) * gi;
+  vi = b2 * vi + (1.0f - b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
-  P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  pi -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  P[i] = pi;
+  pack_param(Q, i, pi);
+}
+
+__global__ void pack_weights_kernel(const float* __restrict__ P, unsigned short* __restrict__ Q) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kSurParams) pack_param(Q, i, P[i]);
 }
 
 // ---------------------------------------------------------------- in the step ----
@@ -445,20 +671,6 @@ __device__ __forceinline__ bool make_features(const RespBox* __restrict__ bxp, d
 __device__ __forceinline__ double approx_factor(double k, double kfs) {
   const double t = 1.0 + k / kfs;
   return 1.0 / (t * t);
-}
-
-__global__ void pack_weights_kernel(const float* __restrict__ P, unsigned short* __restrict__ Q) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kPackW2) {
-    const int o = i / 16, in = i % 16;
-    Q[i] = in < kSurIn ? f2bf(P[kOffW1 + in * 128 + o]) : static_cast<unsigned short>(0);
-  } else if (i < kPackW3) {
-    const int j = i - kPackW2, o = j / 128, in = j % 128;
-    Q[i] = f2bf(P[kOffW2 + in * 128 + o]);
-  } else if (i < kPackSize) {
-    const int j = i - kPackW3, o = j / 128, in = j % 128;
-    Q[i] = f2bf(P[kOffW3 + in * 128 + o]);
-  }
 }
 
 // ---- one row through the network inside a workgroup of RT = 256 threads ----
@@ -722,30 +934,46 @@ __global__ void dataset_kernel(const RespBox* __restrict__ boxes, const double* 
 
 }  // namespace
 
-hipError_t launch_mlp_train(const float* P, const float* x, const float* y, const int* perm,
-                            int64_t row0, int64_t count, float inv_batch, float* grad,
-                            float* loss_sum, hipStream_t s) {
-  const unsigned blocks = static_cast<unsigned>((count + TB - 1) / TB);
-  hipLaunchKernelGGL(mlp_train_kernel, dim3(blocks), dim3(NT), 0, s, P, x, y, perm, row0, count,
-                     inv_batch, grad, loss_sum);
+int64_t mlp_part_floats() { return static_cast<int64_t>(kTrainWGs) * kPartSize; }
+
+// A workgroup per CU (its registers and LDS fill one) walks the tiles. Returns the number of
+// sets of sums in *n_part.
+hipError_t launch_mlp_train(const float* P, const unsigned short* Q, const float* x, const float* y,
+                            const int* perm, int64_t row0, int64_t count, float inv_batch,
+                            float* part, int* n_part, hipStream_t s) {
+  const int64_t tiles = (count + TB - 1) / TB;
+  *n_part = static_cast<int>(std::min<int64_t>(tiles, kTrainWGs));
+  hipLaunchKernelGGL(mlp_train_kernel, dim3(static_cast<unsigned>(*n_part)), dim3(kNetNT), 0, s, P,
+                     Q, x, y, perm, row0, count, inv_batch, part);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_predict(const float* P, const float* x, float* y, int64_t n, hipStream_t s) {
-  const unsigned blocks = static_cast<unsigned>((n + TB - 1) / TB);
-  hipLaunchKernelGGL(mlp_predict_kernel, dim3(blocks), dim3(NT), 0, s, P, x, y, n);
+hipError_t launch_mlp_predict(const float* P, const unsigned short* Q, const float* x, float* y,
+                              int64_t n, hipStream_t s) {
+  const int64_t tiles = (n + TB - 1) / TB;      // two workgroups per CU
+  hipLaunchKernelGGL(mlp_predict_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(tiles, 512))),
+                     dim3(kNetNT), 0, s, P, Q, x, y, n);
   return hipGetLastError();
 }
 
-hipError_t launch_adam(float* P, const float* g, float* m, float* v, int n, float lr, float b1,
-                       float b2, float eps, float c1, float c2, hipStream_t s) {
-  hipLaunchKernelGGL(adam_kernel, dim3((n + 255) / 256), dim3(256), 0, s, P, g, m, v, n, lr, b1,
-                     b2, eps, c1, c2);
+hipError_t launch_mlp_adam(const float* part, int n_part, bool first, float* loss, float* P,
+                           float* m, float* v, unsigned short* Q, float lr, float b1, float b2,
+                           float eps, float c1, float c2, hipStream_t s) {
+  hipLaunchKernelGGL(mlp_reduce_kernel<true>, dim3((kPartVec + 514 + 63) / 64), dim3(256), 0, s, part,
+                     n_part, first ? 1 : 0, loss, nullptr, P, m, v, Q, lr, b1, b2, eps, c1, c2);
+  return hipGetLastError();
+}
+
+hipError_t launch_mlp_gradient(const float* part, int n_part, float* loss, float* grad,
+                               hipStream_t s) {
+  hipLaunchKernelGGL(mlp_reduce_kernel<false>, dim3((kPartVec + 514 + 63) / 64), dim3(256), 0, s,
+                     part, n_part, 1, loss, grad, nullptr, nullptr, nullptr, nullptr, 0.f, 0.f, 0.f,
+                     0.f, 0.f, 0.f);
   return hipGetLastError();
 }
 
 hipError_t launch_pack_weights(const float* P, unsigned short* Q, hipStream_t s) {
-  hipLaunchKernelGGL(pack_weights_kernel, dim3((kPackSize + 255) / 256), dim3(256), 0, s, P, Q);
+  hipLaunchKernelGGL(pack_weights_kernel, dim3((kSurParams + 255) / 256), dim3(256), 0, s, P, Q);
   return hipGetLastError();
 }
 

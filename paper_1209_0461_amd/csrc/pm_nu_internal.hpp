@@ -321,12 +321,20 @@ hipError_t launch_response(const RespBox* boxes, const double* partial, int n_pa
 // threads per workgroup of the exact response for this many (bin, box) pairs: 64 or 256
 int response_threads(int nbins, int nbox);
 // mlp_kernels.hip
-hipError_t launch_mlp_train(const float* P, const float* x, const float* y, const int* perm,
-                            int64_t row0, int64_t count, float inv_batch, float* grad,
-                            float* loss_sum, hipStream_t s);
-hipError_t launch_mlp_predict(const float* P, const float* x, float* y, int64_t n, hipStream_t s);
-hipError_t launch_adam(float* P, const float* g, float* m, float* v, int n, float lr, float b1,
-                       float b2, float eps, float c1, float c2, hipStream_t s);
+// Q: the packed bfloat16 weights of P (launch_pack_weights), which launch_mlp_adam keeps current.
+// launch_mlp_train leaves *n_part sets of gradient sums in part (mlp_part_floats() floats,
+// 16-byte aligned), which launch_mlp_adam or launch_mlp_gradient adds up.
+int64_t mlp_part_floats();
+hipError_t launch_mlp_train(const float* P, const unsigned short* Q, const float* x, const float* y,
+                            const int* perm, int64_t row0, int64_t count, float inv_batch,
+                            float* part, int* n_part, hipStream_t s);
+hipError_t launch_mlp_predict(const float* P, const unsigned short* Q, const float* x, float* y,
+                              int64_t n, hipStream_t s);
+hipError_t launch_mlp_adam(const float* part, int n_part, bool first, float* loss, float* P,
+                           float* m, float* v, unsigned short* Q, float lr, float b1, float b2,
+                           float eps, float c1, float c2, hipStream_t s);
+hipError_t launch_mlp_gradient(const float* part, int n_part, float* loss, float* grad,
+                               hipStream_t s);
 hipError_t launch_pack_weights(const float* P, unsigned short* Q, hipStream_t s);
 int64_t packed_weight_count();
 hipError_t launch_surrogate_response(const float* P, const unsigned short* Q, int mode,

@@ -17,7 +17,7 @@ namespace pmnu {
 
 struct Surrogate {
   float* P = nullptr;          // [kSurBlob] FP32 masters + statistics
-  float* g = nullptr;          // [kSurParams] gradient
+  float* part = nullptr;       // [mlp_part_floats()] gradient sums of the workgroups
   float* m = nullptr;          // [kSurParams] Adam first moment
   float* v = nullptr;          // [kSurParams] Adam second moment
   float* loss = nullptr;       // [1]
@@ -35,7 +35,7 @@ struct Surrogate {
 void surrogate_free(Ctx& c) {
   Surrogate* s = c.sur;
   if (!s) return;
-  void* bufs[] = {s->P, s->g, s->m, s->v, s->loss, s->perm, s->chk_exact, s->chk_sur,
+  void* bufs[] = {s->P, s->part, s->m, s->v, s->loss, s->perm, s->chk_exact, s->chk_sur,
                   s->packed, s->sur_r};
   for (void* p : bufs)
     if (p) (void)hipFree(p);
@@ -51,7 +51,7 @@ int ensure(Ctx& c) {
   c.sur = s;
   const size_t nb = static_cast<size_t>(c.nbox) * c.B;
   hipError_t e = hipMalloc(&s->P, kSurBlob * sizeof(float));
-  if (!e) e = hipMalloc(&s->g, kSurParams * sizeof(float));
+  if (!e) e = hipMalloc(&s->part, mlp_part_floats() * sizeof(float));
   if (!e) e = hipMalloc(&s->m, kSurParams * sizeof(float));
   if (!e) e = hipMalloc(&s->v, kSurParams * sizeof(float));
   if (!e) e = hipMalloc(&s->loss, sizeof(float));
@@ -85,6 +85,16 @@ int need_loaded(Ctx* c) {
   return PM_NU_OK;
 }
 
+// the bfloat16 image of the current weights (training keeps it current by itself)
+int ensure_packed(Ctx& c) {
+  Surrogate* s = c.sur;
+  if (s->packed_valid) return PM_NU_OK;
+  hipError_t e = launch_pack_weights(s->P, s->packed, c.stream);
+  if (e != hipSuccess) return set_error(PM_NU_EHIP, "weight packing: %s", hipGetErrorString(e));
+  s->packed_valid = true;
+  return PM_NU_OK;
+}
+
 #define SUR_LAUNCH(call)                                                                   \
   do {                                                                                     \
     hipError_t e_ = (call);                                                                \
@@ -98,11 +108,8 @@ int surrogate_launch(Ctx& c, int mode, double norm) {
   int rc = need_loaded(&c);
   if (rc) return rc;
   Surrogate* s = c.sur;
-  if (!s->packed_valid) {
-    hipError_t e = launch_pack_weights(s->P, s->packed, c.stream);
-    if (e != hipSuccess) return set_error(PM_NU_EHIP, "weight packing: %s", hipGetErrorString(e));
-    s->packed_valid = true;
-  }
+  rc = ensure_packed(c);
+  if (rc) return rc;
   timer_begin(c, ST_SURROGATE);
   hipError_t e = launch_surrogate_response(
       s->P, s->packed, mode, c.d_resp, c.bin_partial, c.n_partial, c.d_counts, c.d_kmean,
@@ -231,6 +238,8 @@ int pm_nu_surrogate_train_part(pm_nu_ctx* ctx, const float* x, const float* y, i
     PMNU_HIP(hipMalloc(&s->perm, n * sizeof(int)));
     s->perm_cap = n;
   }
+  rc = ensure_packed(*c);
+  if (rc) return rc;
   std::vector<int> perm(n);
   const int64_t nb = (n + batch - 1) / batch;
   const int64_t total = nb * total_epochs;
@@ -245,21 +254,19 @@ int pm_nu_surrogate_train_part(pm_nu_ctx* ctx, const float* x, const float* y, i
     }
     PMNU_HIP(hipStreamSynchronize(c->stream));
     PMNU_HIP(hipMemcpy(s->perm, perm.data(), n * sizeof(int), hipMemcpyHostToDevice));
-    SUR_LAUNCH(launch_fill_zero(s->loss, sizeof(float), c->stream));
     for (int64_t b = 0; b < nb; ++b, ++t) {
       const int64_t r0 = b * batch, cnt = std::min<int64_t>(batch, n - r0);
-      SUR_LAUNCH(launch_fill_zero(s->g, kSurParams * sizeof(float), c->stream));
-      SUR_LAUNCH(launch_mlp_train(s->P, x, y, s->perm, r0, cnt, 1.0f / cnt, s->g, s->loss,
-                                  c->stream));
+      int n_part = 0;
+      SUR_LAUNCH(launch_mlp_train(s->P, s->packed, x, y, s->perm, r0, cnt, 1.0f / cnt, s->part,
+                                  &n_part, c->stream));
       ++s->step;
       const double frac = static_cast<double>(t) / std::max<int64_t>(1, total - 1);
       const float lr_t =
           static_cast<float>(lr * (0.01 + 0.99 * 0.5 * (1.0 + std::cos(kPi * frac))));
       const float c1 = static_cast<float>(1.0 - std::pow(0.9, static_cast<double>(s->step)));
       const float c2 = static_cast<float>(1.0 - std::pow(0.999, static_cast<double>(s->step)));
-      s->packed_valid = false;
-      SUR_LAUNCH(launch_adam(s->P, s->g, s->m, s->v, kSurParams, lr_t, 0.9f, 0.999f, 1e-8f, c1, c2,
-                             c->stream));
+      SUR_LAUNCH(launch_mlp_adam(s->part, n_part, b == 0, s->loss, s->P, s->m, s->v, s->packed,
+                                 lr_t, 0.9f, 0.999f, 1e-8f, c1, c2, c->stream));
     }
     float lsum = 0.f;
     PMNU_HIP(hipStreamSynchronize(c->stream));
@@ -280,7 +287,9 @@ int pm_nu_surrogate_predict(pm_nu_ctx* ctx, const float* x, float* y, int64_t n)
   int rc = need_loaded(c);
   if (rc) return rc;
   if (!x || !y || n < 1) return set_error(PM_NU_EINVAL, "bad arguments");
-  SUR_LAUNCH(launch_mlp_predict(c->sur->P, x, y, n, c->stream));
+  rc = ensure_packed(*c);
+  if (rc) return rc;
+  SUR_LAUNCH(launch_mlp_predict(c->sur->P, c->sur->packed, x, y, n, c->stream));
   return PM_NU_OK;
 }
 
@@ -291,11 +300,12 @@ int pm_nu_surrogate_grad(pm_nu_ctx* ctx, const float* x, const float* y, int64_t
   if (rc) return rc;
   if (!x || !y || !grad || n < 1) return set_error(PM_NU_EINVAL, "bad arguments");
   Surrogate* s = c->sur;
-  SUR_LAUNCH(launch_fill_zero(s->g, kSurParams * sizeof(float), c->stream));
-  SUR_LAUNCH(launch_fill_zero(s->loss, sizeof(float), c->stream));
-  SUR_LAUNCH(launch_mlp_train(s->P, x, y, nullptr, 0, n, 1.0f / n, s->g, s->loss, c->stream));
-  PMNU_HIP(hipMemcpyAsync(grad, s->g, kSurParams * sizeof(float), hipMemcpyDeviceToDevice,
-                          c->stream));
+  rc = ensure_packed(*c);
+  if (rc) return rc;
+  int n_part = 0;
+  SUR_LAUNCH(launch_mlp_train(s->P, s->packed, x, y, nullptr, 0, n, 1.0f / n, s->part, &n_part,
+                              c->stream));
+  SUR_LAUNCH(launch_mlp_gradient(s->part, n_part, s->loss, grad, c->stream));
   float lsum = 0.f;
   PMNU_HIP(hipStreamSynchronize(c->stream));
   PMNU_HIP(hipMemcpy(&lsum, s->loss, sizeof(float), hipMemcpyDeviceToHost));
