@@ -159,8 +159,8 @@ int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles, int n_mesh
 
 /* ---- diagnostics (copies of internal state, enqueued on the stream) ---------------- */
 /* (sync) How many chunk parts the patch deposit (deposit modes 6..9) has sent through its
- * atomic side grid since the last call (a chunk whose bounding box exceeds the LDS tile,
- * or its part in a coarse cell whose patch list was full); 0 when every chunk went
+ * atomic side grid since the last call (a chunk whose bounding box exceeds a patch's 26624
+ * nodes, or its part in a coarse cell whose patch list was full); 0 when every chunk went
  * through its patch, and always 0 for the other deposit modes. */
 int pm_nu_side_grid_uses(pm_nu_ctx* ctx, int64_t* uses);
 /* Deposited mass rho (unit mass per particle) of one box into out (dev) [N][N][N].
@@ -249,9 +249,10 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
  * deposit_block = threads per workgroup), 1..5 (LDS-privatised chunks of 1024/2048/4096
  * particles on 256 threads, 4096 on 512 threads, 8192 on 1024 threads, flushed with global
  * atomics; mode 4 takes 512 on 256 threads for N <= 32 and for few particles), 6 (chunks of 4096 written to per-chunk patches and summed per 16^3 coarse
- * cell without atomics; a chunk whose box exceeds 6144 nodes, or its part in a coarse cell
- * already listing 32 patches, goes through atomics on a side grid),
- * 7 (as 6 with room for boxes of 9216 nodes, at lower occupancy), 8 and 9 (as 6 and 7 with
+ * cell without atomics; a box beyond the LDS tile's 6144 nodes takes several
+ * passes; a chunk whose box exceeds 26624 nodes, or its part in a coarse cell already listing
+ * 32 patches, goes through atomics on a side grid),
+ * 7 (as 6 with a tile of 9216 nodes, at lower occupancy), 8 and 9 (as 6 and 7 with
  * the coarse-cell sums and the first forward FFT pass in one kernel, so that delta never
  * goes to HBM; N >= 32), interp_mode
  * 0 (direct gather; interp_block = particles per workgroup, rounded down to 256, 512 or

@@ -1497,7 +1497,7 @@ hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const in
                               const int4* reg_list, unsigned long long* rho_fb, const int* n_fb,
                               float2* out, const float2* tw, double scale, int nbox,
                               hipStream_t s, float* delta_out) {
-  return dispatch_n<PatchFwdZ>(n, patches, kPatchCap, reg_count, reg_list, rho_fb, n_fb, out, tw,
+  return dispatch_n<PatchFwdZ>(n, patches, kPatchSlot, reg_count, reg_list, rho_fb, n_fb, out, tw,
                                scale, nbox, s, delta_out);
 }
 hipError_t launch_fwd_x_bin(int n, float2* data, const float2* tw, const uint16_t* bin_of_n2,

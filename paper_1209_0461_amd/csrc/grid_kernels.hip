@@ -21,6 +21,8 @@
 // (particles in arbitrary order) take the per-particle global-atomic path instead, so
 // the result does not depend on the order; the speed does. Particles kept along a
 // space-filling curve (as tree codes keep them) give compact chunks.
+#include <type_traits>
+
 #include "patch_device.hpp"
 
 namespace pmnu {
@@ -37,10 +39,11 @@ __device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int&
   i = static_cast<int>(__double2loint(f + 6755399441055744.0)) & nmask;
 }
 
-// Round-to-nearest-even of 0 <= v < 2^52 as an integer: adding 2^52 leaves the rounded
-// value in the low mantissa bits (same result as __double2ll_rn, far fewer instructions).
-__device__ __forceinline__ unsigned long long fix_rn(double v) {
-  return static_cast<unsigned long long>(__double_as_longlong(v + 4503599627370496.0)) -
+// The product a b, 0 <= a b < 2^52, rounded to the nearest integer (ties to even): adding 2^52
+// in one fused operation leaves it in the low mantissa bits; only the high word needs the
+// exponent taken off.
+__device__ __forceinline__ unsigned long long fix_product(double a, double b) {
+  return static_cast<unsigned long long>(__double_as_longlong(fma(a, b, 4503599627370496.0))) -
          0x4330000000000000ull;
 }
 
@@ -74,8 +77,8 @@ __device__ __forceinline__ void deposit_global(unsigned long long* g, int n, con
       const int iy = (i[1] + cy) & nmask;
       const double wxy = wx[cx] * wy[cy];
       const unsigned row = (static_cast<unsigned>(ix) * n + iy) * n;
-      atomicAdd(g + row + iz0, fix_rn(wxy * (1.0 - d[2])));
-      atomicAdd(g + row + iz1, fix_rn(wxy * d[2]));
+      atomicAdd(g + row + iz0, fix_product(wxy, 1.0 - d[2]));
+      atomicAdd(g + row + iz1, fix_product(wxy, d[2]));
     }
   }
 }
@@ -117,95 +120,289 @@ __device__ __forceinline__ int wave_max(int v) {
   return v;
 }
 
-// Chunk of PPT * 256 consecutive particles held in registers (lower node and fraction per
-// axis) and the periodic bounding box of their lower nodes relative to the first particle's
-// node. Every thread computes the same reference node, so no barrier is needed for it.
-// With KEEP the lower node (relative to r, three 10-bit fields offset by 512) and the FP32
-// fraction of every particle are kept, so users need not find them again.
+// Largest / smallest of three, one instruction each; a NaN operand is passed over.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// max with the lane that a DPP control selects (lanes without one keep their value)
+template <int CTRL>
+__device__ __forceinline__ float max_dpp(float v) {
+  const int i = __float_as_int(v);
+  const float o = __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+  return o > v ? o : v;
+}
+// over groups of 8 lanes (every lane gets it): pairs, quads, halves of a row
+__device__ __forceinline__ float max8(float v) {
+  return max_dpp<0x141>(max_dpp<0x4e>(max_dpp<0xb1>(v)));
+}
+// over the wave, in lane 63: rows of 16, then the two broadcasts of a row's last lane
+__device__ __forceinline__ float wave_max63(float v) {
+  return max_dpp<0x143>(max_dpp<0x142>(max_dpp<0x140>(max8(v))));
+}
+
+// PPT * NT consecutive particles held in registers and the periodic box of their lower nodes
+// and upper neighbours: origin g0 (a mesh index) and extent ext <= n nodes per axis. full: an
+// axis is covered whole (ext = n), where the upper neighbour of the last node is the first.
+// ok: bit q set when particle tid + q NT exists and is finite.
 template <int PPT>
 struct Chunk {
   float p[PPT][3];
-  bool ok[PPT];
-  int rel[PPT];
-  float f[PPT][3];
-  int r[3];
-  int mn[3], ext[3];   // box origin (relative to r) and extent in nodes, upper neighbours included
-  bool any;
+  unsigned ok;
+  int g0[3], ext[3];
+  bool any, full, bad;
+};
+struct ChunkRed {
+  float m[7][16];   // per wave: -min and max of each axis, then a NaN mark
+  int i[6][16];
 };
 
-template <int PPT, int NT = 256, bool KEEP = false>
-__device__ __forceinline__ void load_chunk(Chunk<PPT>& c, const float* p, int cnt, double inv_cell,
-                                           int nmask, int (*red)[NT / 64], bool& bad) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, half = (nmask + 1) / 2;
+// floor(x inv_cell) is monotone in x, so the box of a chunk that does not wrap around the
+// mesh is that of its smallest and largest coordinates: three v_min3 / v_max3 pairs for two
+// particles, where finding every particle's node took 12 instructions an axis. A chunk with
+// a non-finite coordinate, or whose nodes span half the mesh or more (it may wrap), takes the
+// nodes of every particle relative to the first one's instead; the two give the same box
+// where both apply. One barrier, two more in the second form.
+template <int PPT, int NT>
+__device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt, double inv_cell,
+                                          int nmask, ChunkRed& red) {
+  constexpr int NW = NT / 64;
+  static_assert(PPT % 2 == 0 && NW <= 16, "pairs of particles; at most 16 waves");
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, n = nmask + 1, half = n / 2;
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    const int j = tid + q * NT, js = j < cnt ? j : 0;   // the first one again beyond the end
+    c.p[q][0] = p[3 * js];
+    c.p[q][1] = p[3 * js + 1];
+    c.p[q][2] = p[3 * js + 2];
+  }
+  float mn[3], mx[3], sum = 0.f;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) mn[a] = mx[a] = c.p[0][a];
+#pragma unroll
+  for (int q = 0; q < PPT; q += 2) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      mn[a] = min3(mn[a], c.p[q][a], c.p[q + 1][a]);
+      mx[a] = max3(mx[a], c.p[q][a], c.p[q + 1][a]);
+      sum += c.p[q][a];
+      sum += c.p[q + 1][a];
+    }
+  }
+  // an infinity shows in mn or mx, a NaN in the sum
+  const bool nan = __any(!(sum == sum));
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const float lo = wave_max63(-mn[a]), hi = wave_max63(mx[a]);
+    if (lane == 63) {
+      red.m[a][wv] = lo;
+      red.m[3 + a][wv] = hi;
+    }
+  }
+  if (lane == 63) red.m[6][wv] = nan ? 1.f : 0.f;
+  __syncthreads();
+  // lanes 8 a .. 8 a + 7 of every wave reduce quantity a over the waves and turn it to a node
+  const int a8 = min(lane >> 3, 6), w8 = lane & 7;
+  float v = red.m[a8][NW >= 8 ? w8 : w8 & (NW - 1)];
+  if constexpr (NW > 8) v = fmaxf(v, red.m[a8][w8 + 8]);
+  v = max8(v);
+  const double u = floor(static_cast<double>(a8 < 3 ? -v : v) * inv_cell);
+  const int node = fabs(u) < 1073741824.0 ? static_cast<int>(u) : 0x7fffffff;
+  bool fast = __builtin_amdgcn_readlane(__float_as_int(v), 48) == 0;
+  c.any = true;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int lo = __builtin_amdgcn_readlane(node, 8 * a);
+    const int hi = __builtin_amdgcn_readlane(node, 24 + 8 * a);
+    fast = fast && lo != 0x7fffffff && hi != 0x7fffffff && hi - lo < half;
+    c.g0[a] = lo & nmask;
+    c.ext[a] = hi - lo + 2;
+  }
+  c.ok = 0u;
+  c.bad = false;
+  c.full = false;
+  if (fast) {
+#pragma unroll
+    for (int q = 0; q < PPT; ++q) c.ok |= tid + q * NT < cnt ? 1u << q : 0u;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) c.full = c.full || c.ext[a] >= n;   // n = 8: 5 + 2 never
+    return;
+  }
+  int r[3];
   {
     const float x = p[0], y = p[1], z = p[2];
     const bool ok0 = finite3(x, y, z);
-    double dd;
-    axis64(ok0 ? x : 0.f, inv_cell, nmask, c.r[0], dd);
-    axis64(ok0 ? y : 0.f, inv_cell, nmask, c.r[1], dd);
-    axis64(ok0 ? z : 0.f, inv_cell, nmask, c.r[2], dd);
+    double d;
+    axis64(ok0 ? x : 0.f, inv_cell, nmask, r[0], d);
+    axis64(ok0 ? y : 0.f, inv_cell, nmask, r[1], d);
+    axis64(ok0 ? z : 0.f, inv_cell, nmask, r[2], d);
   }
+  int in[3] = {1 << 30, 1 << 30, 1 << 30}, ix[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
 #pragma unroll
   for (int q = 0; q < PPT; ++q) {
-    const int j = tid + q * NT;
-    c.p[q][0] = c.p[q][1] = c.p[q][2] = 0.f;
-    if (j < cnt) {
-      c.p[q][0] = p[3 * j];
-      c.p[q][1] = p[3 * j + 1];
-      c.p[q][2] = p[3 * j + 2];
-    }
-  }
-  int mn[3] = {1 << 30, 1 << 30, 1 << 30}, mx[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
+    const bool here = tid + q * NT < cnt;
+    const bool ok = here && finite3(c.p[q][0], c.p[q][1], c.p[q][2]);
+    c.bad |= here && !ok;
+    if (!ok) continue;
+    c.ok |= 1u << q;
 #pragma unroll
-  for (int q = 0; q < PPT; ++q) {
-    const int j = tid + q * NT;
-    c.ok[q] = j < cnt && finite3(c.p[q][0], c.p[q][1], c.p[q][2]);
-    bad |= (j < cnt) && !c.ok[q];
-    if (KEEP) c.rel[q] = 0;
-    if (c.ok[q]) {
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        int i;
-        double d;
-        axis64(c.p[q][a], inv_cell, nmask, i, d);
-        const int rel = ((i - c.r[a] + half) & nmask) - half;
-        mn[a] = min(mn[a], rel);
-        mx[a] = max(mx[a], rel);
-        if (KEEP) {
-          c.rel[q] |= (rel + 512) << (10 * a);      // -256 <= rel < 256
-          c.f[q][a] = static_cast<float>(d);
-        }
-      }
+    for (int a = 0; a < 3; ++a) {
+      int i;
+      double d;
+      axis64(c.p[q][a], inv_cell, nmask, i, d);
+      const int rel = ((i - r[a] + half) & nmask) - half;
+      in[a] = min(in[a], rel);
+      ix[a] = max(ix[a], rel);
     }
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    mn[a] = wave_min(mn[a]);
-    mx[a] = wave_max(mx[a]);
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      red[a][wv] = mn[a];
-      red[3 + a][wv] = mx[a];
+    in[a] = wave_min(in[a]);
+    ix[a] = wave_max(ix[a]);
+    if (lane == 0) {
+      red.i[a][wv] = in[a];
+      red.i[3 + a][wv] = ix[a];
     }
   }
   __syncthreads();
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-      mn[a] = min(mn[a], red[a][w]);
-      mx[a] = max(mx[a], red[3 + a][w]);
+    for (int w = 0; w < NW; ++w) {
+      in[a] = min(in[a], red.i[a][w]);
+      ix[a] = max(ix[a], red.i[3 + a][w]);
     }
+    in[a] = __builtin_amdgcn_readfirstlane(in[a]);
+    ix[a] = __builtin_amdgcn_readfirstlane(ix[a]);
   }
-  // the box is the same for the whole workgroup: keep it in scalar registers
-  c.any = __builtin_amdgcn_readfirstlane(mn[0] <= mx[0] ? 1 : 0) != 0;
+  c.any = in[0] <= ix[0];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    c.r[a] = __builtin_amdgcn_readfirstlane(c.r[a]);
-    c.mn[a] = __builtin_amdgcn_readfirstlane(mn[a]);
-    c.ext[a] = c.any ? __builtin_amdgcn_readfirstlane(mx[a] - mn[a] + 2) : 0;
+    c.ext[a] = c.any ? ix[a] - in[a] + 2 : 0;
+    c.g0[a] = (__builtin_amdgcn_readfirstlane(r[a]) + in[a]) & nmask;
+    if (c.ext[a] >= n) {
+      c.ext[a] = n;
+      c.g0[a] = 0;
+      c.full = true;
+    }
+  }
+}
+
+// A particle's lower node relative to the box origin and its fraction on one axis; mg is
+// kFloorMagic - g0, so that the node comes out relative to g0 in one addition.
+constexpr double kFloorMagic = 6755399441055744.0;     // 1.5 * 2^52
+__device__ __forceinline__ void box_axis(float x, double inv_cell, double mg, int nmask, int& t,
+                                         double& d) {
+  const double u = static_cast<double>(x) * inv_cell;
+  const double f = floor(u);
+  d = u - f;
+  t = static_cast<int>(__double2loint(f + mg)) & nmask;
+}
+
+// Strides of an ey x ez plane in an LDS tile: padded so that a wave's 16-lane groups of
+// particles along the curve (2 x 2 x 4 blocks of nodes for lattice-ordered chunks) hit 16
+// distinct 8-byte bank slots, z stride = 4 (mod 8), y stride = 2 (mod 4), unless a tile of cap
+// nodes would then hold fewer planes of an ex-plane box than it takes passes without. (256^3:
+// unpadded strides cost the deposit 25 M bank-conflict cycles, 85 against 77 us.)
+struct TileStrides {
+  int sy, sz, npl;                     // npl: planes per pass, 0 if not one plane fits
+};
+__device__ __forceinline__ TileStrides tile_strides(int ex, int ey, int ez, int cap) {
+  TileStrides t;
+  t.sz = ez + ((12 - ez % 8) % 8);
+  t.sy = ey + ((6 - ey % 4) % 4);
+  const int plane = ey * ez;
+  const int plain = plane > 0 && plane <= cap ? min(ex, cap / plane) : 0;
+  const int padded = plane > 0 && t.sy * t.sz <= cap ? min(ex, cap / (t.sy * t.sz)) : 0;
+  t.npl = padded;
+  if (padded == 0 || (plain > padded && (ex + plain - 1) / plain < (ex + padded - 1) / padded)) {
+    t.sy = ey;
+    t.sz = ez;
+    t.npl = plain;
+  }
+  return t;
+}
+
+// The chunk's fixed-point weights added to the planes [p0, p0 + npl) of its box in tile
+// ([plane][sy][sz]) with 64-bit LDS atomics. WHOLE: the planes are the whole box and no axis
+// wraps inside it; otherwise every plane is checked and the upper neighbours wrap.
+template <bool WHOLE, int PPT>
+__device__ __forceinline__ void add_chunk(const Chunk<PPT>& c, unsigned long long* tile,
+                                          double inv_cell, int nmask, int sy, int sz, int p0,
+                                          int npl) {
+  const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2], plane = sy * sz;
+  const double mx = kFloorMagic - c.g0[0], my = kFloorMagic - c.g0[1], mz = kFloorMagic - c.g0[2];
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    if (!((c.ok >> q) & 1u)) continue;
+    int t[3];
+    double d[3];
+    box_axis(c.p[q][0], inv_cell, mx, nmask, t[0], d[0]);
+    if constexpr (!WHOLE) {
+      const int up = t[0] + 1 < ex ? t[0] + 1 : 0;
+      if (static_cast<unsigned>(t[0] - p0) >= static_cast<unsigned>(npl) &&
+          static_cast<unsigned>(up - p0) >= static_cast<unsigned>(npl))
+        continue;
+    }
+    box_axis(c.p[q][1], inv_cell, my, nmask, t[1], d[1]);
+    box_axis(c.p[q][2], inv_cell, mz, nmask, t[2], d[2]);
+    const double wx[2] = {(1.0 - d[0]) * kFixScale, d[0] * kFixScale};
+    const double wy[2] = {1.0 - d[1], d[1]};
+    const double wz[2] = {1.0 - d[2], d[2]};
+    if constexpr (WHOLE) {
+      const int base = (t[0] * sy + t[1]) * sz + t[2];
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) {
+#pragma unroll
+        for (int cy = 0; cy < 2; ++cy) {
+          const double wxy = wx[cx] * wy[cy];
+          const int o = base + cx * plane + cy * sz;
+          atomicAdd(&tile[o], fix_product(wxy, wz[0]));
+          atomicAdd(&tile[o + 1], fix_product(wxy, wz[1]));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int cx = 0; cx < 2; ++cx) {
+        const int lx = (t[0] + cx < ex ? t[0] + cx : 0) - p0;
+        if (static_cast<unsigned>(lx) >= static_cast<unsigned>(npl)) continue;
+#pragma unroll
+        for (int cy = 0; cy < 2; ++cy) {
+          const double wxy = wx[cx] * wy[cy];
+          const int row = (lx * sy + (t[1] + cy < ey ? t[1] + cy : 0)) * sz;
+          atomicAdd(&tile[row + t[2]], fix_product(wxy, wz[0]));
+          atomicAdd(&tile[row + (t[2] + 1 < ez ? t[2] + 1 : 0)], fix_product(wxy, wz[1]));
+        }
+      }
+    }
+  }
+}
+
+// v nodes of the tile cleared, 16 bytes a store (tile 16-byte aligned, its size even)
+template <int NT>
+__device__ __forceinline__ void clear_tile(unsigned long long* tile, int v) {
+  ulonglong2* t2 = reinterpret_cast<ulonglong2*>(tile);
+  for (int t = threadIdx.x; t < (v + 1) / 2; t += NT) t2[t] = make_ulonglong2(0ull, 0ull);
+}
+
+// the chunk's particles straight to the grid g with global atomics
+template <int PPT>
+__device__ __forceinline__ void add_chunk_global(const Chunk<PPT>& c, unsigned long long* g, int n,
+                                                 double inv_cell, int nmask) {
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    if (!((c.ok >> q) & 1u)) continue;
+    int i[3];
+    double d[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) axis64(c.p[q][a], inv_cell, nmask, i[a], d[a]);
+    deposit_global(g, n, i, d, nmask);
   }
 }
 
@@ -253,103 +450,67 @@ __global__ __launch_bounds__(NT) void deposit_tiled_kernel(const float* __restri
                                                            int* __restrict__ flags,
                                                            int64_t chunks_per_box) {
   constexpr int PPT = CH / NT;
-  __shared__ unsigned long long tile[CAP];
-  __shared__ int red[6][NT / 64];
-  const int tid = threadIdx.x;
+  __shared__ alignas(16) unsigned long long tile[CAP];
+  __shared__ ChunkRed red;
   const int64_t box = blockIdx.x / chunks_per_box;
   const int64_t c0 = (blockIdx.x - box * chunks_per_box) * CH;
   const int cnt = static_cast<int>(min(static_cast<int64_t>(CH), np - c0));
   const int nmask = n - 1;
   unsigned long long* g = rho + box * static_cast<int64_t>(n) * n * n;
   Chunk<PPT> c;
-  bool bad = false;
-  load_chunk<PPT, NT>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red, bad);
-  if (bad) atomicOr(flags, 1);
+  chunk_box<PPT, NT>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red);
+  if (c.bad) atomicOr(flags, 1);
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2];
-  // Tile strides padded so that a wave's 16-lane groups of particles along the curve
-  // (2 x 2 x 4 blocks of nodes for lattice-ordered chunks) hit 16 distinct 8-byte bank
-  // slots: z stride = 4 (mod 8), y stride = 2 (mod 4). Unpadded if the padding does not fit.
-  int sz = ez + ((12 - ez % 8) % 8), sy = ey + ((6 - ey % 4) % 4);
-  if (ex * sy * sz > CAP) {
-    sz = ez;
-    sy = ey;
-  }
-  const int vol = ex * sy * sz;
-  if (c.any && vol <= CAP && ex <= n && ey <= n && ez <= n) {
-    for (int t = tid; t < vol; t += NT) tile[t] = 0ull;
+  const TileStrides ts = tile_strides(ex, ey, ez, CAP);
+  if (c.any && ts.npl == ex) {
+    clear_tile<NT>(tile, ex * ts.sy * ts.sz);
     __syncthreads();
-    const int half = n / 2;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      if (!c.ok[q]) continue;
-      int t[3];
-      double d[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        int i;
-        axis64(c.p[q][a], inv_cell, nmask, i, d[a]);
-        t[a] = ((i - c.r[a] + half) & nmask) - half - c.mn[a];
-      }
-      const double wx[2] = {(1.0 - d[0]) * kFixScale, d[0] * kFixScale};
-      const double wy[2] = {1.0 - d[1], d[1]};
-      const double wz0 = 1.0 - d[2], wz1 = d[2];
-      const int base = (t[0] * sy + t[1]) * sz + t[2];
-#pragma unroll
-      for (int cx = 0; cx < 2; ++cx) {
-#pragma unroll
-        for (int cy = 0; cy < 2; ++cy) {
-          const double wxy = wx[cx] * wy[cy];
-          const int o = base + (cx * sy + cy) * sz;
-          atomicAdd(&tile[o], fix_rn(wxy * wz0));
-          atomicAdd(&tile[o + 1], fix_rn(wxy * wz1));
-        }
-      }
-    }
+    if (c.full) add_chunk<false>(c, tile, inv_cell, nmask, ts.sy, ts.sz, 0, ex);
+    else add_chunk<true>(c, tile, inv_cell, nmask, ts.sy, ts.sz, 0, ex);
     __syncthreads();
-    const int gx0 = c.r[0] + c.mn[0], gy0 = c.r[1] + c.mn[1], gz0 = c.r[2] + c.mn[2];
     for_box_nodes<NT>(ex, ey, ez, [&](int tx, int ty, int tz, int) {
-      const unsigned long long v = tile[(tx * sy + ty) * sz + tz];
+      const unsigned long long v = tile[(tx * ts.sy + ty) * ts.sz + tz];
       if (v == 0ull) return;
-      const unsigned gx = (gx0 + tx) & nmask, gy = (gy0 + ty) & nmask, gz = (gz0 + tz) & nmask;
+      const unsigned gx = (c.g0[0] + tx) & nmask, gy = (c.g0[1] + ty) & nmask,
+                     gz = (c.g0[2] + tz) & nmask;
       atomicAdd(g + (gx * n + gy) * n + gz, v);
     });
   } else {
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      if (!c.ok[q]) continue;
-      int i[3];
-      double d[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) axis64(c.p[q][a], inv_cell, nmask, i[a], d[a]);
-      deposit_global(g, n, i, d, nmask);
-    }
+    add_chunk_global(c, g, n, inv_cell, nmask);
   }
 }
 
 // ---------------------------------------------------------------- patch deposit ----
 // Deposit without global atomics. D1: each chunk sums its particles in an LDS tile as
-// above, writes the tile (its box, unpadded) to its own patch slot with plain stores and
-// registers the patch in every coarse cell (CB^3 nodes) that the box overlaps; a registry
-// entry carries everything D2 needs (chunk, box origin, extents). D2: one workgroup per
-// slab of a coarse cell adds up the registered patches in exact integers and writes
-// delta = rho / rho_bar - 1 once, rounded to FP32. Weights that cannot go through a patch
-// (a box too large: the whole chunk; a coarse cell whose list is full: the box's part in
-// that cell) are added with global atomics to a side grid kept at zero, which D2 folds in
-// (and clears) only when something was added to it.
+// above, writes the tile to its own patch slot with plain stores and registers the patch in
+// every coarse cell (CB^3 nodes) that the box overlaps; a registry entry carries everything
+// D2 needs (chunk, box origin, extents). A box larger than the tile is summed in passes over
+// as many of its x-planes as fit, the particles staying in registers, up to the slot's
+// kPatchSlot nodes. D2: one workgroup per slab of a coarse cell adds up the registered patches
+// in exact integers and writes delta = rho / rho_bar - 1 once, rounded to FP32. Weights that
+// cannot go through a patch (a box too large: the whole chunk; a coarse cell whose list is
+// full: the box's part in that cell) are added with global atomics to a side grid kept at
+// zero, which D2 folds in (and clears) only when something was added to it: one atomic per
+// non-zero node of a box up to kSideBoxMax nodes, eight per particle beyond.
 
 __device__ __forceinline__ int ceil_div_pow2(int a, int lg) { return (a + (1 << lg) - 1) >> lg; }
 
+// Bound at 256^3 (lattice order, boxes of about 17^3) by the bytes it moves, 365 MB: 77 us, 72 at
+// the copy rate; 84 before the box was found from the extreme coordinates (42 M VALU
+// instructions, now 34 M). Boxes beyond the tile, us before (per-particle atomics) and now:
+// displacements of 1 and 2 cells 1555 -> 102 and 3600 -> 132, C order 803 -> 166.
 template <int CH, int CAP, int NT>
-__global__ __launch_bounds__(NT) void deposit_patch_kernel(
+__global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 2) void deposit_patch_kernel(
     const float* __restrict__ pos, unsigned long long* __restrict__ patches,
     int* __restrict__ reg_count, int4* __restrict__ reg_list,
     unsigned long long* __restrict__ rho_fb, int* __restrict__ n_fb,
     int64_t np, int n, double inv_cell, int* __restrict__ flags, int64_t chunks_per_box,
     int cb_lg) {
-  constexpr int PPT = CH / NT;
-  __shared__ unsigned long long tile[CAP];
-  __shared__ int red[6][NT / 64];
-  __shared__ unsigned s_over;          // bit t: registry cell t of the box was full
+  constexpr int PPT = CH / NT, OVER = (kPatchRegMax + 31) / 32;
+  constexpr int TILE = CAP + kPatchPad;
+  __shared__ alignas(16) unsigned long long tile[TILE];
+  __shared__ ChunkRed red;
+  __shared__ unsigned s_over[OVER];    // bit t: registry cell t of the box was full
   const int tid = threadIdx.x;
   const int64_t chunk = blockIdx.x;
   // grid sizes stay below 2^31 blocks: a 32-bit division suffices
@@ -359,128 +520,104 @@ __global__ __launch_bounds__(NT) void deposit_patch_kernel(
   const int nmask = n - 1;
   const int64_t m = static_cast<int64_t>(n) * n * n;
   unsigned long long* fb = rho_fb + box * m;
-  if (tid == 0) s_over = 0u;
+  if (tid < OVER) s_over[tid] = 0u;
   Chunk<PPT> c;
-  bool bad = false;
-  load_chunk<PPT, NT>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red, bad);
-  if (bad) atomicOr(flags, 1);
+  chunk_box<PPT, NT>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red);
+  if (c.bad) atomicOr(flags, 1);
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2];
-  int sz = ez + ((12 - ez % 8) % 8), sy = ey + ((6 - ey % 4) % 4);
-  if (ex * sy * sz > CAP) {
-    sz = ez;
-    sy = ey;
-  }
-  const int vol = ex * sy * sz;
-  const int gx0 = (c.r[0] + c.mn[0]) & nmask, gy0 = (c.r[1] + c.mn[1]) & nmask,
-            gz0 = (c.r[2] + c.mn[2]) & nmask;
-  const int nc = n >> cb_lg;
-  const int rx = min(nc, ceil_div_pow2((gx0 & ((1 << cb_lg) - 1)) + ex, cb_lg));
-  const int ry = min(nc, ceil_div_pow2((gy0 & ((1 << cb_lg) - 1)) + ey, cb_lg));
-  const int rz = min(nc, ceil_div_pow2((gz0 & ((1 << cb_lg) - 1)) + ez, cb_lg));
-  const bool fits = c.any && vol <= CAP && ex <= n && ey <= n && ez <= n &&
-                    rx * ry * rz <= kPatchRegMax;
-  if (fits) {
-    // register the patch in the coarse cells its box overlaps (origin and extents < 1024)
-    const int64_t cells = static_cast<int64_t>(nc) * nc * nc;
-    const int fx = gx0 >> cb_lg, fy = gy0 >> cb_lg, fz = gz0 >> cb_lg;
-    const int4 entry = make_int4(static_cast<int>(chunk), gx0 | (gy0 << 10) | (gz0 << 20),
-                                 ex | (ey << 10) | (ez << 20), 0);
-    for (int t = tid; t < rx * ry * rz; t += NT) {
-      const int iz = t % rz, ixy = t / rz, iy = ixy % ry, ix = ixy / ry;
-      const int64_t cell = box * cells +
-                           ((static_cast<int64_t>((fx + ix) % nc) * nc + (fy + iy) % nc) * nc +
-                            (fz + iz) % nc);
-      const int slot = atomicAdd(reg_count + cell, 1);
-      if (slot < kPatchList)
-        reg_list[cell * kPatchList + slot] = entry;
-      else
-        atomicOr(&s_over, 1u << t);             // t < kPatchRegMax <= 32
-    }
-    for (int t = tid; t < vol; t += NT) tile[t] = 0ull;
-    __syncthreads();
-    const int half = n / 2;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      if (!c.ok[q]) continue;
-      int t[3];
-      double d[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        int i;
-        axis64(c.p[q][a], inv_cell, nmask, i, d[a]);
-        t[a] = ((i - c.r[a] + half) & nmask) - half - c.mn[a];
-      }
-      const double wx[2] = {(1.0 - d[0]) * kFixScale, d[0] * kFixScale};
-      const double wy[2] = {1.0 - d[1], d[1]};
-      const double wz0 = 1.0 - d[2], wz1 = d[2];
-      const int base = (t[0] * sy + t[1]) * sz + t[2];
-#pragma unroll
-      for (int cx = 0; cx < 2; ++cx) {
-#pragma unroll
-        for (int cy = 0; cy < 2; ++cy) {
-          const double wxy = wx[cx] * wy[cy];
-          const int o = base + (cx * sy + cy) * sz;
-          atomicAdd(&tile[o], fix_rn(wxy * wz0));
-          atomicAdd(&tile[o + 1], fix_rn(wxy * wz1));
-        }
+  const int plane = ey * ez, vol = ex * plane;         // < 2^28
+  const int gx0 = c.g0[0], gy0 = c.g0[1], gz0 = c.g0[2];
+  const TileStrides ts = tile_strides(ex, ey, ez, TILE);
+  const int sy = ts.sy, sz = ts.sz, npl = c.any ? ts.npl : 0;   // npl: planes per pass
+  const int nc = n >> cb_lg, cbm = (1 << cb_lg) - 1;
+  const int rx = min(nc, ceil_div_pow2((gx0 & cbm) + ex, cb_lg));
+  const int ry = min(nc, ceil_div_pow2((gy0 & cbm) + ey, cb_lg));
+  const int rz = min(nc, ceil_div_pow2((gz0 & cbm) + ez, cb_lg));
+  const bool patch = npl > 0 && vol <= kPatchSlot && rx * ry * rz <= kPatchRegMax;
+  bool side = true;                    // something of the chunk goes to the side grid
+  if (patch || (npl > 0 && vol <= kSideBoxMax)) {
+    if (patch) {
+      // register the patch in the coarse cells its box overlaps (origin and extents < 1024)
+      const int64_t cells = static_cast<int64_t>(nc) * nc * nc;
+      const int fx = gx0 >> cb_lg, fy = gy0 >> cb_lg, fz = gz0 >> cb_lg;
+      const int4 entry = make_int4(static_cast<int>(chunk), gx0 | (gy0 << 10) | (gz0 << 20),
+                                   ex | (ey << 10) | (ez << 20), 0);
+      for (int t = tid; t < rx * ry * rz; t += NT) {
+        const int iz = t % rz, ixy = t / rz, iy = ixy % ry, ix = ixy / ry;
+        const int64_t cell = box * cells +
+                             ((static_cast<int64_t>((fx + ix) % nc) * nc + (fy + iy) % nc) * nc +
+                              (fz + iz) % nc);
+        const int slot = atomicAdd(reg_count + cell, 1);
+        if (slot < kPatchList)
+          reg_list[cell * kPatchList + slot] = entry;
+        else
+          atomicOr(&s_over[t >> 5], 1u << (t & 31));   // t < kPatchRegMax
       }
     }
-    __syncthreads();
-    // the patch (the box unpadded): consecutive lanes at consecutive nodes, four nodes per
-    // thread per round with their LDS reads ahead of the stores. Node li of the box is
-    // (tx, ty, tz) = (li / (ey ez), li / ez % ey, li % ez); the FP32 quotients are exact
-    // (li < 2^14 and the fractional part of (li + 1/2) / e is at least 1 / (2e)).
-    unsigned long long* pat = patches + chunk * kPatchCap;     // stored patch stride
-    {
-      const int volp = ex * ey * ez;
-      const float inv_ez = 1.0f / static_cast<float>(ez), inv_ey = 1.0f / static_cast<float>(ey);
-      for (int l0 = tid; l0 < volp; l0 += 4 * NT) {
-        unsigned long long val[4];
+    unsigned long long* pat = patches + chunk * kPatchSlot;
+    for (int p0 = 0; p0 < ex; p0 += npl) {
+      const int npp = min(npl, ex - p0);
+      clear_tile<NT>(tile, npp * sy * sz);
+      __syncthreads();
+      // the positions made opaque in every pass: the particles' nodes and weights are formed
+      // again instead of being kept over the passes (which took 254 registers)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int li = l0 + u * NT;
-          val[u] = 0ull;
-          if (li < volp) {
-            const int t = static_cast<int>((static_cast<float>(li) + 0.5f) * inv_ez);
-            const int tz = li - t * ez;
-            const int tx = static_cast<int>((static_cast<float>(t) + 0.5f) * inv_ey);
-            const int ty = t - tx * ey;
-            val[u] = tile[(tx * sy + ty) * sz + tz];
+      for (int q = 0; q < PPT; ++q)
+        asm volatile("" : "+v"(c.p[q][0]), "+v"(c.p[q][1]), "+v"(c.p[q][2]));
+      if (npl == ex && !c.full) add_chunk<true>(c, tile, inv_cell, nmask, sy, sz, 0, ex);
+      else add_chunk<false>(c, tile, inv_cell, nmask, sy, sz, p0, npp);
+      __syncthreads();
+      unsigned over = 0u;
+      if (patch) {
+        // the patch (the box unpadded): consecutive lanes at consecutive nodes, four nodes per
+        // thread per round with their LDS reads ahead of the stores. Node li of the pass lies
+        // in row li / ez and plane li / ez / ey; the FP32 quotients are exact (li < 2^14, and
+        // the fractional part of (li + 1/2) / e is at least 1 / (2e)).
+        unsigned long long* dst = pat + p0 * plane;
+        const int tv = npp * plane, pad_z = sz - ez, pad_y = (sy - ey) * sz;
+        const float inv_ez = 1.0f / static_cast<float>(ez), inv_ey = 1.0f / static_cast<float>(ey);
+        for (int l0 = tid; l0 < tv; l0 += 4 * NT) {
+          unsigned long long val[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int li = l0 + u * NT;
+            const int row = static_cast<int>(fmaf(static_cast<float>(li), inv_ez, 0.5f * inv_ez));
+            const int pl = static_cast<int>(fmaf(static_cast<float>(row), inv_ey, 0.5f * inv_ey));
+            val[u] = li < tv ? tile[li + row * pad_z + pl * pad_y] : 0ull;
           }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (l0 + u * NT < tv) dst[l0 + u * NT] = val[u];
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (l0 + u * NT < volp) pat[l0 + u * NT] = val[u];
+        for (int w = 0; w < OVER; ++w) over |= s_over[w];
+        side = over != 0u;
       }
+      if (side) {
+        // to the side grid: the whole box, or (a patch) its part in the cells whose list was full
+        for_box_nodes<NT>(npp, ey, ez, [&](int lx, int ty, int tz, int) {
+          const int tx = p0 + lx;
+          if (patch) {
+            int ix = ((gx0 & cbm) + tx) >> cb_lg, iy = ((gy0 & cbm) + ty) >> cb_lg,
+                iz = ((gz0 & cbm) + tz) >> cb_lg;
+            ix -= ix >= nc ? nc : 0;                // a box as wide as the mesh wraps onto fx
+            iy -= iy >= nc ? nc : 0;
+            iz -= iz >= nc ? nc : 0;
+            const int t = (ix * ry + iy) * rz + iz;
+            if (!((s_over[t >> 5] >> (t & 31)) & 1u)) return;
+          }
+          const unsigned long long v = tile[(lx * sy + ty) * sz + tz];
+          if (v == 0ull) return;
+          const unsigned gx = (gx0 + tx) & nmask, gy = (gy0 + ty) & nmask, gz = (gz0 + tz) & nmask;
+          atomicAdd(fb + (gx * n + gy) * n + gz, v);
+        });
+      }
+      if (p0 + npl < ex) __syncthreads();           // the tile is read before the next pass clears it
     }
-    const unsigned over = s_over;
-    if (over == 0u) return;
-    // coarse cells whose list was full: the box's part in them goes to the side grid
-    const int cbm = (1 << cb_lg) - 1;
-    for_box_nodes<NT>(ex, ey, ez, [&](int tx, int ty, int tz, int) {
-      int ix = ((gx0 & cbm) + tx) >> cb_lg, iy = ((gy0 & cbm) + ty) >> cb_lg,
-          iz = ((gz0 & cbm) + tz) >> cb_lg;
-      ix -= ix >= nc ? nc : 0;                  // a box as wide as the mesh wraps onto fx
-      iy -= iy >= nc ? nc : 0;
-      iz -= iz >= nc ? nc : 0;
-      if (!((over >> ((ix * ry + iy) * rz + iz)) & 1u)) return;
-      const unsigned long long v = tile[(tx * sy + ty) * sz + tz];
-      if (v == 0ull) return;
-      const unsigned gx = (gx0 + tx) & nmask, gy = (gy0 + ty) & nmask, gz = (gz0 + tz) & nmask;
-      atomicAdd(fb + (gx * n + gy) * n + gz, v);
-    });
   } else {
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-      if (!c.ok[q]) continue;
-      int i[3];
-      double d[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) axis64(c.p[q][a], inv_cell, nmask, i[a], d[a]);
-      deposit_global(fb, n, i, d, nmask);
-    }
+    add_chunk_global(c, fb, n, inv_cell, nmask);
   }
-  if (tid == 0) atomicAdd(n_fb, 1);
+  if (side && tid == 0) atomicAdd(n_fb, 1);
 }
 
 // D2: one workgroup of 256 threads per (slab of XD x-planes of a coarse cell, box), CB =
@@ -808,7 +945,7 @@ __global__ __launch_bounds__(256) void interp_kernel(const float* pos,
 // Interpolation with the chunk's box of the acceleration grid staged in LDS (rows of
 // 3 * ez consecutive floats); chunks whose box does not fit gather straight from HBM.
 template <int CH, int CAP, bool LEAP>
-__global__ __launch_bounds__(256) void interp_tiled_kernel(const float* pos,
+__global__ __launch_bounds__(256, CH <= 1024 ? 6 : 1) void interp_tiled_kernel(const float* pos,
                                                            const float* __restrict__ force,
                                                            float* __restrict__ acc, int64_t np,
                                                            int n, double inv_cell,
@@ -816,7 +953,7 @@ __global__ __launch_bounds__(256) void interp_tiled_kernel(const float* pos,
                                                            int64_t nchunks, Leap lp) {
   constexpr int NT = 256, PPT = CH / NT;
   __shared__ float tile[CAP * 3];
-  __shared__ int red[6][256 / 64];
+  __shared__ ChunkRed red;
   const int tid = threadIdx.x;
   const int64_t chunk = xcd_chunk(blockIdx.x, gridDim.x);
   if (chunk >= nchunks) return;
@@ -832,13 +969,27 @@ __global__ __launch_bounds__(256) void interp_tiled_kernel(const float* pos,
     dd = static_cast<float>(lp.kd[2 * box + 1]);
   }
   Chunk<PPT> c;
-  bool bad = false;
-  load_chunk<PPT, 256, true>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red, bad);
+  chunk_box<PPT, 256>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red);
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2];
   const int vol = ex * ey * ez;
-  const bool use_tile = c.any && vol <= CAP && ex <= n && ey <= n && ez <= n;
+  const bool use_tile = c.any && vol <= CAP && !c.full;
+  // every particle's node in the box (three 10-bit fields) and fraction
+  int rel[PPT];
+  float fr[PPT][3];
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) {
+    rel[q] = 0;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      int t;
+      double d;
+      box_axis(c.p[q][a], inv_cell, kFloorMagic - c.g0[a], nmask, t, d);
+      rel[q] |= t << (10 * a);
+      fr[q][a] = static_cast<float>(d);
+    }
+  }
   if (use_tile) {
-    const int gx0 = c.r[0] + c.mn[0], gy0 = c.r[1] + c.mn[1], gz0 = c.r[2] + c.mn[2];
+    const int gx0 = c.g0[0], gy0 = c.g0[1], gz0 = c.g0[2];
     constexpr int RMAX = 32;                 // rows per wave held in registers
     const int rows = ex * ey;
     if (3 * ez <= 64 && rows <= 4 * RMAX) {
@@ -884,19 +1035,16 @@ __global__ __launch_bounds__(256) void interp_tiled_kernel(const float* pos,
     const int j = tid + q * NT;
     if (j >= cnt) continue;
     float a0 = 0.f, a1 = 0.f, a2 = 0.f;
-    if (c.ok[q]) {
+    if ((c.ok >> q) & 1u) {
       Corner k;                                  // from the node and fraction kept above
-      int rel[3];
+      int t[3];
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        rel[a] = ((c.rel[q] >> (10 * a)) & 1023) - 512;
-        k.w[a][1] = c.f[q][a];
+        t[a] = (rel[q] >> (10 * a)) & 1023;
+        k.w[a][1] = fr[q][a];
         k.w[a][0] = 1.0f - k.w[a][1];
       }
       if (use_tile) {
-        int t[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) t[a] = rel[a] - c.mn[a];
         const int base = (t[0] * ey + t[1]) * ez + t[2];
 #pragma unroll
         for (int cx = 0; cx < 2; ++cx) {
@@ -915,7 +1063,7 @@ __global__ __launch_bounds__(256) void interp_tiled_kernel(const float* pos,
         }
       } else {
 #pragma unroll
-        for (int a = 0; a < 3; ++a) k.i[a] = (c.r[a] + rel[a]) & nmask;
+        for (int a = 0; a < 3; ++a) k.i[a] = (c.g0[a] + t[a]) & nmask;
         gather_global(g, n, nmask, k, a0, a1, a2);
       }
     }
@@ -1030,14 +1178,17 @@ hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, i
   if (n > 1024) return hipErrorInvalidValue;     // registry entries pack indices in 10 bits
   const int64_t chunks = patch_chunks(np);
   const dim3 grid(static_cast<unsigned>(chunks * nbox));
-  if (big_tile)
-    hipLaunchKernelGGL((deposit_patch_kernel<kPatchCH, kPatchCap, kPatchNT>), grid,
-                       dim3(kPatchNT), 0, s, pos, patches, reg_count, reg_list, rho_fb, n_fb,
-                       np, n, inv_cell, flags, chunks, patch_cb_log2(n));
-  else
-    hipLaunchKernelGGL((deposit_patch_kernel<kPatchCH, kPatchTile, kPatchNT>), grid,
-                       dim3(kPatchNT), 0, s, pos, patches, reg_count, reg_list, rho_fb, n_fb,
-                       np, n, inv_cell, flags, chunks, patch_cb_log2(n));
+  const auto launch = [&](auto tile) {
+    constexpr int TILE = decltype(tile)::value;
+    hipLaunchKernelGGL((deposit_patch_kernel<kPatchCH, TILE, kPatchNT>), grid, dim3(kPatchNT), 0, s,
+                       pos, patches, reg_count, reg_list, rho_fb, n_fb, np, n, inv_cell, flags,
+                       chunks, patch_cb_log2(n));
+  };
+  // one 64^3 box (64 chunks): 13.2 -> 13.4 us for boxes of one pass, 20.8 -> 18.8 (displaced by
+  // two cells) and 24.2 -> 19.2 (C order) for those that the smaller tile takes several for
+  if (chunks * nbox <= kPatchFewChunks) launch(std::integral_constant<int, kPatchFewTile>{});
+  else if (big_tile) launch(std::integral_constant<int, kPatchCap>{});
+  else launch(std::integral_constant<int, kPatchTile>{});
   return hipGetLastError();
 }
 
@@ -1045,12 +1196,17 @@ hipError_t launch_patch_reduce(const unsigned long long* patches, const int* reg
                                const int4* reg_list, unsigned long long* rho_fb,
                                const int* n_fb, float* delta, int nbox, int n, double scale,
                                hipStream_t s) {
-  // slabs of 8 x-planes: half a 16^3 cell (a whole 8^3 one)
-  const int slabs = (1 << patch_cb_log2(n)) / 8;
-  hipLaunchKernelGGL(patch_reduce_kernel<8>,
-                     dim3(static_cast<unsigned>(patch_coarse_cells(n) * slabs), nbox), dim3(256),
-                     0, s, patches, kPatchCap, reg_count, reg_list, rho_fb, n_fb, delta, n,
-                     patch_cb_log2(n), scale);
+  // slabs of 8 x-planes, half a 16^3 cell (a whole 8^3 one); of 2 where those leave the chip's
+  // 256 CUs fewer than two workgroups each (one 64^3 box 10.1 -> 8.7 us, in C order 20.8 -> 10.5)
+  const int cells = static_cast<int>(patch_coarse_cells(n)), cb = 1 << patch_cb_log2(n);
+  const auto launch = [&](auto xd) {
+    constexpr int XD = decltype(xd)::value;
+    hipLaunchKernelGGL(patch_reduce_kernel<XD>, dim3(static_cast<unsigned>(cells * (cb / XD)), nbox),
+                       dim3(256), 0, s, patches, kPatchSlot, reg_count, reg_list, rho_fb, n_fb,
+                       delta, n, patch_cb_log2(n), scale);
+  };
+  if (static_cast<int64_t>(cells) * (cb / 8) * nbox < 512) launch(std::integral_constant<int, 2>{});
+  else launch(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

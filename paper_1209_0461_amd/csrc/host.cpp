@@ -584,7 +584,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   {
     const size_t chunks = nb * static_cast<size_t>(patch_chunks(c->Np));
     const size_t coarse = nb * static_cast<size_t>(patch_coarse_cells(c->N));
-    ALLOC(c->patches, chunks * kPatchCap);
+    ALLOC(c->patches, chunks * kPatchSlot);
     ALLOC(c->reg_count, coarse);
     ALLOC(c->reg_list, coarse * 32);
     ALLOC(c->rho_fb, nb * c->M);

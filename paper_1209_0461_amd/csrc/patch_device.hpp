@@ -9,7 +9,7 @@
 namespace pmnu {
 
 constexpr int kPatchList = 32;      // patches per coarse cell
-constexpr int kPatchRegMax = 27;    // coarse cells per patch
+constexpr int kPatchRegMax = 96;    // coarse cells per patch
 
 // Up to two pieces of the overlap of a periodic patch interval [p, p + e) with the cell
 // interval [cs, cs + cb) on an axis of length n (e <= n): patch-local start, cell-local

@@ -166,7 +166,7 @@ struct Ctx {
   float* inv_w2 = nullptr;         // [N] 1/sinc^4(pi n/N) per axis index (or 1)
   int* d_flags = nullptr;          // [1] bit 0: non-finite position seen
   // patch deposit (deposit modes 6 and 7)
-  unsigned long long* patches = nullptr;   // [chunks][kPatchCap] per-chunk tiles
+  unsigned long long* patches = nullptr;   // [chunks][kPatchSlot] per-chunk patches
   int* reg_count = nullptr;        // [nbox][coarse cells] patches registered
   int4* reg_list = nullptr;        // [nbox][coarse cells][32] (chunk, origin, extents, 0)
   unsigned long long* rho_fb = nullptr;    // [nbox][M] side grid, kept at zero
@@ -234,12 +234,18 @@ void surrogate_free(Ctx& c);
 constexpr double kFixScale = 1099511627776.0;   // 2^40: fixed-point unit of the deposit
 constexpr int kMaxBins = 1024;                   // largest n_kbins
 static_assert(kMaxBins <= (1 << kRatioBinBits), "bin index of the packed ratio index");
-// patch deposit (deposit mode 6): chunk of particles, LDS tile / patch capacity in nodes,
-// threads per workgroup
 // patch deposit: chunks of kPatchCH particles on kPatchNT threads; the LDS tile holds
-// kPatchTile nodes (mode 6, three workgroups per CU) or kPatchCap (mode 7, room for larger
-// boxes); a stored patch has room for kPatchCap nodes
+// kPatchTile nodes (mode 6, three workgroups per CU) or kPatchCap (mode 7, two); a stored
+// patch has room for kPatchSlot nodes, summed in several passes beyond the tile: a 16^3 block
+// whose halo is six nodes a side (28^3), or 16 rows of 256 particles in C order (5 x 20 x 256)
 constexpr int kPatchCH = 4096, kPatchCap = 9216, kPatchTile = 6144, kPatchNT = 512;
+constexpr int kPatchPad = 448;       // more room in the tile for padded strides (18 x 18 x 20)
+constexpr int kPatchSlot = 26624;
+// up to one chunk per CU a workgroup has a CU to itself and takes most of its LDS
+constexpr int kPatchFewChunks = 256, kPatchFewTile = 18432;
+// largest box that goes to the side grid node by node: 8 nodes a particle, what the particles
+// would add one by one
+constexpr int kSideBoxMax = 8 * kPatchCH;
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);
 hipError_t launch_fixed_to_float(const unsigned long long* src, float* dst, int64_t n,
                                  hipStream_t s);
