@@ -210,8 +210,8 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
                                       c->tw, scale, c->nbox, c->stream, v);
           case 1: return launch_fwd_y(c->N, c->ck[1], c->ck[2], c->tw, c->nbox, c->stream, v);
           case 2:
-            return launch_fwd_x_bin(c->N, c->ck[0], c->tw, c->bin_of_n2, c->bin_partial, c->B,
-                                    c->nbox, c->stream, v);
+            return launch_fwd_x_bin(c->N, c->ck[0], c->tw, c->bin_of_n2, c->d_edges, c->bin_partial,
+                                    c->B, c->nbox, c->stream, v);
           case 3:
             return launch_inv_x(c->N, c->ck[0], c->ck[1], c->ck[2], c->tw, c->ridx, c->d_next,
                                 c->ratio, c->d_resp, c->B, c->inv_w2, cgreen, kf, c->nbox,

@@ -42,14 +42,18 @@ namespace pmnu {
 namespace {
 
 constexpr int NT = 256;
+constexpr int kBinCopyBytes = 2048;
 
 template <int N> struct Shape {
   static constexpr int NK = N / 2 + 1;
   static constexpr int FZ_TY = N <= 32 ? N : (N <= 256 ? 32 : 16);   // real rows per WG
   static constexpr int FY_NL = N <= 256 ? (N < 16 ? N : 16) : 8;      // rows per WG
-  static constexpr int FX_TX = N < 16 ? N : (N <= 256 ? 16 : 8);      // ky columns per WG
-  static constexpr int IX_TX = N < 16 ? N : 8;
-  static constexpr int IY_NL = N < 8 ? N : 4;
+  // N = 64: wider tiles for the passes along x (64 boxes, us: fwd_x 16 -> 32 columns 24.6 -> 21.0,
+  // inv_x 8 -> 16 53 -> 40; one box the same either way); N = 512: two lines in inv_y, whose
+  // LDS then admits six workgroups a CU (530 -> 500)
+  static constexpr int FX_TX = N < 16 ? N : N == 64 ? 32 : (N <= 256 ? 16 : 8);   // ky columns per WG
+  static constexpr int IX_TX = N < 16 ? N : N == 64 ? 16 : 8;
+  static constexpr int IY_NL = N < 8 ? N : N == 512 ? 2 : 4;
   static constexpr int IZ_TY = N < 16 ? N : (N <= 256 ? 16 : 8);
 };
 
@@ -66,8 +70,10 @@ template <int N> struct Tiles {
                                                                           : Shape<N>::FY_NL / 4)};
   static constexpr int FX[3] = {Shape<N>::FX_TX, alt(Shape<N>::FX_TX, Shape<N>::FX_TX == 16 ? 8 : 16),
                                 alt(Shape<N>::FX_TX, Shape<N>::FX_TX == 16 ? 32 : 4)};
-  static constexpr int IX[3] = {Shape<N>::IX_TX, alt(Shape<N>::IX_TX, 4), alt(Shape<N>::IX_TX, 16)};
-  static constexpr int IY[3] = {Shape<N>::IY_NL, alt(Shape<N>::IY_NL, 2), alt(Shape<N>::IY_NL, 8)};
+  static constexpr int IX[3] = {Shape<N>::IX_TX, alt(Shape<N>::IX_TX, 4),
+                                alt(Shape<N>::IX_TX, Shape<N>::IX_TX == 16 ? 8 : 16)};
+  static constexpr int IY[3] = {Shape<N>::IY_NL, alt(Shape<N>::IY_NL, Shape<N>::IY_NL == 2 ? 4 : 2),
+                                alt(Shape<N>::IY_NL, 8)};
   static constexpr int IZ[3] = {Shape<N>::IZ_TY, alt(Shape<N>::IZ_TY, Shape<N>::IZ_TY == 16 ? 8 : 16),
                                 alt(Shape<N>::IZ_TY, Shape<N>::IZ_TY == 16 ? 32 : 4)};
 };
@@ -630,17 +636,32 @@ __global__ __launch_bounds__(kFwdZYNT) void fwd_zy_kernel(const void* __restrict
   }
 }
 
+// Copies of the LDS bins of fwd_x_bin_kernel: neighbouring k_y columns mostly add to the same
+// bin, so each adds to the copy of its column; 2 KB of them leave the workgroups per CU as they
+// are (one copy: 256^3 25.7 against 24.5 us, 64 boxes of 64^3 26.3 against 24.6; 8 KB of copies
+// cost a workgroup a CU and 3 us).
+__host__ __device__ constexpr int bin_copies(int nbins) {
+  int c = 1;
+  while (c < 16 && 2 * c * nbins * 8 <= kBinCopyBytes) c *= 2;
+  return c;
+}
+
 // STORE: write the transformed tile back (only for reading the modes out); BIN: the mode
 // sums per k-bin (the step bins without storing; the inverse pass redoes the x transform).
+// bin_of_n2: the bin of every integer |n|^2; edges [nbins + 1]: the bins' |n|^2 edges.
+// Its reads alone take 11 us at 256^3 and 90 at 512^3. With a bin looked up per mode (64 lanes,
+// 64 lines of a table beyond the L1) and every mode added by itself the kernel took 26 and 262 us;
+// modes k_x and -k_x together, one lookup per run of them and the bins' edges in LDS: 22 and 187.
 template <int N, bool STORE, bool BIN, int TX>
 __global__ __launch_bounds__(NT) void fwd_x_bin_kernel(float2* __restrict__ data,
                                                        const float2* __restrict__ twg,
                                                        const uint16_t* __restrict__ bin_of_n2,
+                                                       const int* __restrict__ edges,
                                                        double* __restrict__ partial, int nbins) {
   constexpr int ES = TX + 1, NK = Shape<N>::NK;
   __shared__ float2 lds[N * ES];
   __shared__ float2 tw[N];
-  extern __shared__ double bins[];
+  extern __shared__ double bins[];                     // [bin][copy], then the edges
   // workgroups go to the 8 XCDs in turn; the remap gives each XCD a contiguous run of
   // (k_y block, k_z) tiles of a box, so that the workgroups reading the two halves of a
   // 128-byte line (TX = 8) share one L2
@@ -650,24 +671,27 @@ __global__ __launch_bounds__(NT) void fwd_x_bin_kernel(float2* __restrict__ data
   if (tile >= NYB * NK) return;
   const int y0 = (tile % NYB) * TX, kz = tile / NYB, box = blockIdx.y;
   load_twiddles<N, NT>(tw, twg);
-  if constexpr (BIN)
-    for (int b = threadIdx.x; b < nbins; b += NT) bins[b] = 0.0;
-  // binning: thread t walks a run of RUN consecutive k_x at k_y = y0 + t % TX, where |n|^2
-  // changes slowly; the run's bin indices are fetched here so that their latency hides
-  // behind the loads and the transform (-1: no mode)
+  // binning: thread t walks a run of RUN consecutive k_x in [0, N/2) at k_y = y0 + t % TX, each
+  // with -k_x (the same |n|^2; k_x = 0 is alone, and N/2 is added by itself). The bin of the
+  // run's first mode is fetched here, behind the tile's loads; from there on the thread steps
+  // through the bins' edges.
   constexpr int RUNS = NT / TX;                        // runs per k_y column
-  constexpr int RUN = (N + RUNS - 1) / RUNS;           // k_x values per run
+  constexpr int RUN = (N / 2 + RUNS - 1) / RUNS;       // k_x values per run
   static_assert(TX * RUNS == NT, "one run per thread");
   [[maybe_unused]] const int by = threadIdx.x % TX, bx0 = (threadIdx.x / TX) * RUN;
-  [[maybe_unused]] int bk[RUN];
+  [[maybe_unused]] int s2 = 0, cur = 0, cur_n = 0;
   if constexpr (BIN) {
     const int ny = signed_index(y0 + by, N);
-#pragma unroll
-    for (int u = 0; u < RUN; ++u) {
-      const int nx = signed_index(bx0 + u, N);
-      const int n2 = nx * nx + ny * ny + kz * kz;
-      bk[u] = (bx0 + u < N && n2 > 0) ? static_cast<int>(bin_of_n2[n2]) : -1;
-    }
+    s2 = ny * ny + kz * kz;
+    cur = bin_of_n2[bx0 < N / 2 ? bx0 * bx0 + s2 : 0];
+    if (bx0 == 0) cur_n = bin_of_n2[N / 2 * (N / 2) + s2];
+  }
+  [[maybe_unused]] const int copies = bin_copies(nbins);
+  [[maybe_unused]] int* s_edge = reinterpret_cast<int*>(bins + nbins * copies);
+  if constexpr (BIN) {
+    for (int b = threadIdx.x; b < nbins * copies; b += NT) bins[b] = 0.0;
+    // (the last bin has no upper edge)
+    for (int b = threadIdx.x; b <= nbins; b += NT) s_edge[b] = b < nbins ? edges[b] : 0x7fffffff;
   }
   float2* base = data + ((static_cast<size_t>(box) * NK + kz) * N) * N + y0;
   // float4 = two consecutive k_y; all loads in flight before the LDS stores
@@ -701,30 +725,40 @@ __global__ __launch_bounds__(NT) void fwd_x_bin_kernel(float2* __restrict__ data
     }
   }
   if constexpr (!BIN) return;
-  {
-    int cur = -1;
+  if (bx0 < N / 2) {
+    double* mine = bins + (by & (copies - 1));
+    auto power = [&](int x) {
+      const float2 v = lds[x * ES + by];
+      return w * (static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y);
+    };
+    int hi = s_edge[cur + 1];
     double acc = 0.0;
 #pragma unroll
     for (int u = 0; u < RUN; ++u) {
-      const int b = bk[u];
-      if (b < 0) continue;
-      const float2 v = lds[(bx0 + u) * ES + by];
-      const double p = w * (static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y);
-      if (b != cur) {
-        if (cur >= 0) atomicAdd(&bins[cur], acc);
-        cur = b;
+      const int x = bx0 + u, n2 = x * x + s2;          // grows along the run
+      double p = x > 0 ? power(x) + power(N - x) : (s2 > 0 ? power(0) : 0.0);   // not the mean
+      if (n2 >= hi) {
+        atomicAdd(mine + cur * copies, acc);
         acc = 0.0;
+        do {
+          hi = s_edge[++cur + 1];
+        } while (n2 >= hi);
       }
       acc += p;
     }
-    if (cur >= 0) atomicAdd(&bins[cur], acc);
+    atomicAdd(mine + cur * copies, acc);
+    if (bx0 == 0) atomicAdd(mine + cur_n * copies, power(N / 2));
   }
   __syncthreads();
   // partial sums stored bin-major, [box][bin][workgroup], for contiguous reads per bin
   const int wg = tile;
   const size_t n_wg = static_cast<size_t>(NYB) * NK;
   double* dst = partial + static_cast<size_t>(box) * nbins * n_wg + wg;
-  for (int b = threadIdx.x; b < nbins; b += NT) dst[b * n_wg] = bins[b];
+  for (int b = threadIdx.x; b < nbins; b += NT) {
+    double v = bins[b * copies];
+    for (int c = 1; c < copies; ++c) v += bins[b * copies + c];
+    dst[b * n_wg] = v;
+  }
 }
 
 // ------------------------------------------------------------------------ inverse ----
@@ -785,17 +819,21 @@ __global__ __launch_bounds__(kInvXNT<N>) void inv_x_kernel(const float2* __restr
   const size_t off = ((static_cast<size_t>(box) * NK + kz) * N) * N + y0;
   const float wz = inv_w2[kz];
   const double fnu = boxes[box].f_nu;
-  // where n^2 of this thread's Green's-function modes falls among the bins, fetched before
-  // the tile so that the gathers' latency hides behind its loads
-  constexpr int GI = (N * TX + NT - 1) / NT;
-  uint32_t ri[GI];
+  // Green's function: thread t takes the modes x and N - x (the same n^2) of k_y column t % TX,
+  // x < N/2; x = 0 goes with N/2. Where their n^2 falls among the bins is fetched before the
+  // tile, so that the gathers' latency hides behind its loads. (A gather per mode instead
+  // of per pair: 503 against 479 us at 512^3.)
+  constexpr int GI = (N / 2 * TX + NT - 1) / NT;
+  static_assert(N / 2 * TX % NT == 0 || N / 2 * TX < NT, "pairs cover the threads evenly");
+  uint32_t ri[GI], rn = 0;                         // rn: x = N/2 (the threads that have x = 0)
 #pragma unroll
   for (int i = 0; i < GI; ++i) {
     const int t = threadIdx.x + i * NT;
     const int y = t % TX, x = t / TX;
-    const int nx = signed_index(x, N), ny = signed_index(y0 + y, N);
-    const int n2 = nx * nx + ny * ny + kz * kz;
-    ri[i] = ridx[t < N * TX ? n2 : 0];
+    const int ny = signed_index(y0 + y, N);
+    const int n2 = x * x + ny * ny + kz * kz;
+    ri[i] = ridx[t < N / 2 * TX ? n2 : 0];
+    if (i == 0 && x == 0) rn = ridx[n2 + N / 2 * (N / 2)];
   }
   // the tile holds x (real space) by k_y: forward transform along x first (lines 0..TX-1)
   constexpr int P = TX / 2, IT = (N * P + NT - 1) / NT;
@@ -819,25 +857,32 @@ __global__ __launch_bounds__(kInvXNT<N>) void inv_x_kernel(const float2* __restr
   float tv[GI];                                    // T(n^2) (unused at the k = 0 mode)
 #pragma unroll
   for (int i = 0; i < GI; ++i) tv[i] = neutrino_factor(ri[i], s_r, nbins, fnu);
+  const float tn = neutrino_factor(rn, s_r, nbins, fnu);
   fft_lines<N, TX, NT, -1, ES>(lds, tw);
   // delta_M -> phi and -i k_x phi, in place on the (k_x, k_y) tile
 #pragma unroll
   for (int i = 0; i < GI; ++i) {
     const int t = threadIdx.x + i * NT;
-    if (t >= N * TX) break;
-    const int y = t % TX, x = t / TX;
-    const int nx = signed_index(x, N), ny = signed_index(y0 + y, N);
-    const int n2 = nx * nx + ny * ny + kz * kz;
-    float2 phi = make_float2(0.f, 0.f);
-    if (n2 > 0) {
-      // phi = -C T(n^2) delta / (k^2 W^2), k^2 = kf^2 n^2
-      const float g = -c * tv[i] * s_iw[x] * s_iw[y0 + y] * wz /
-                      (kf * kf * static_cast<float>(n2));
-      phi = cscale(lds[x * ES + y], g);
+    if (t >= N / 2 * TX) break;
+    const int y = t % TX, xp = t / TX;
+    const int ny = signed_index(y0 + y, N);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int x = h == 0 ? xp : (xp == 0 ? N / 2 : N - xp);
+      const int nx = signed_index(x, N);
+      const int n2 = nx * nx + ny * ny + kz * kz;
+      float2 phi = make_float2(0.f, 0.f);
+      if (n2 > 0) {
+        // phi = -C T(n^2) delta / (k^2 W^2), k^2 = kf^2 n^2
+        const float tf = h == 1 && xp == 0 ? tn : tv[i];
+        const float g = -c * tf * s_iw[x] * s_iw[y0 + y] * wz /
+                        (kf * kf * static_cast<float>(n2));
+        phi = cscale(lds[x * ES + y], g);
+      }
+      const float kx = (x == N / 2) ? 0.f : kf * static_cast<float>(nx);
+      lds[x * ES + y] = phi;
+      lds[x * ES + TX + y] = make_float2(kx * phi.y, -kx * phi.x);     // -i k_x phi
     }
-    const float kx = (x == N / 2) ? 0.f : kf * static_cast<float>(nx);
-    lds[x * ES + y] = phi;
-    lds[x * ES + TX + y] = make_float2(kx * phi.y, -kx * phi.x);     // -i k_x phi
   }
   __syncthreads();
   fft_lines<N, NL, NT, +1>(lds, tw);
@@ -1343,7 +1388,7 @@ template <int N> struct FwdZY {
 };
 template <int N> struct FwdX {
   // partial != NULL: bin without storing (the step); NULL: store the modes, no binning
-  static hipError_t run(float2* data, const float2* tw, const uint16_t* bins, double* partial,
+  static hipError_t run(float2* data, const float2* tw, const uint16_t* table, const int* edges, double* partial,
                         int nbins, int nbox, hipStream_t s, int v) {
     auto go = [&](auto tx) -> hipError_t {
       constexpr int TX = decltype(tx)::value;
@@ -1351,10 +1396,11 @@ template <int N> struct FwdX {
       dim3 grid((tiles + 7) / 8 * 8, nbox);          // whole rounds over the 8 XCDs
       if (partial)
         hipLaunchKernelGGL((fwd_x_bin_kernel<N, false, true, TX>), grid, dim3(NT),
-                           nbins * sizeof(double), s, data, tw, bins, partial, nbins);
+                           nbins * bin_copies(nbins) * sizeof(double) + (nbins + 1) * sizeof(int), s,
+                           data, tw, table, edges, partial, nbins);
       else
         hipLaunchKernelGGL((fwd_x_bin_kernel<N, true, false, TX>), grid, dim3(NT), 0, s, data,
-                           tw, bins, partial, nbins);
+                           tw, table, edges, partial, nbins);
       return hipGetLastError();
     };
     return with_tile<PMNU_TILES(FX)>(go, v);
@@ -1501,8 +1547,9 @@ hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const in
                                scale, nbox, s, delta_out);
 }
 hipError_t launch_fwd_x_bin(int n, float2* data, const float2* tw, const uint16_t* bin_of_n2,
-                            double* partial, int nbins, int nbox, hipStream_t s, int v) {
-  return dispatch_n<FwdX>(n, data, tw, bin_of_n2, partial, nbins, nbox, s, v);
+                            const int* edges, double* partial, int nbins, int nbox, hipStream_t s,
+                            int v) {
+  return dispatch_n<FwdX>(n, data, tw, bin_of_n2, edges, partial, nbins, nbox, s, v);
 }
 int fwd_x_partials(int n, int v) {
   int out = 0;

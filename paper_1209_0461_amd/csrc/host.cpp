@@ -127,7 +127,7 @@ int dalloc(T** p, size_t count) {
 
 void free_ctx(Ctx* c);
 
-// Bin geometry (host_math.cpp) and its table of bins per integer |n|^2 on the device.
+// Bin geometry (host_math.cpp), its table of bins per integer |n|^2 and its edges on the device.
 void build_bins(Ctx& c) {
   BinGeometry g = make_bin_geometry(c.N, c.cfg.box_size, c.B);
   c.edges = g.edges;
@@ -136,6 +136,8 @@ void build_bins(Ctx& c) {
   c.nonempty = g.nonempty;
   hipMemcpy(c.bin_of_n2, g.bin_of_n2.data(), g.bin_of_n2.size() * sizeof(uint16_t),
             hipMemcpyHostToDevice);
+  const std::vector<int> edges(g.edges.begin(), g.edges.end());
+  hipMemcpy(c.d_edges, edges.data(), edges.size() * sizeof(int), hipMemcpyHostToDevice);
 }
 
 // Node list of one box for a response at a_now: the stored nodes strictly before a_now
@@ -344,7 +346,7 @@ int do_deposit(Ctx& c, const float* pos) {
                                     fused ? c.reg_count : nullptr, fused ? n_cells : 0));
   // the number of partial bin sums follows the tile of this pass
   c.n_partial = fwd_x_partials(c.N, c.tune.fft[2]);
-  TIMED(c, ST_FFT_X_BIN, launch_fwd_x_bin(c.N, c.ck[0], c.tw, c.bin_of_n2, c.bin_partial,
+  TIMED(c, ST_FFT_X_BIN, launch_fwd_x_bin(c.N, c.ck[0], c.tw, c.bin_of_n2, c.d_edges, c.bin_partial,
                                           c.B, c.nbox, c.stream, c.tune.fft[2]));
   c.stage = 1;
   c.modes_valid = true;
@@ -447,7 +449,7 @@ void free_ctx(Ctx* c) {
   for (hipEvent_t e : c->timer.pool) hipEventDestroy(e);
   void* bufs[] = {c->rho, c->ck[0], c->ck[1], c->ck[2], c->ck[3], c->ck[4], c->force,
                   c->bin_partial,
-                  c->bin_of_n2, c->d_counts, c->d_kmean, c->d_lnk, c->d_nonempty, c->pcdm, c->pnu,
+                  c->bin_of_n2, c->d_edges, c->d_counts, c->d_kmean, c->d_lnk, c->d_nonempty, c->pcdm, c->pnu,
                   c->ratio, c->hist_pm, c->hist_pnu, c->ic_pnu, c->ic_theta, c->tg_ds,
                   c->tg_l2, c->tg_w, c->d_resp, c->ridx, c->d_next, c->tw, c->inv_w2,
                   c->d_flags, c->patches, c->reg_count, c->reg_list, c->rho_fb, c->n_fb,
@@ -561,6 +563,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   ALLOC(c->force, 3 * nb * c->M);
   ALLOC(c->bin_partial, nb * c->n_partial_cap * B);
   ALLOC(c->bin_of_n2, static_cast<size_t>(c->n2max) + 1);
+  ALLOC(c->d_edges, B + 1);
   ALLOC(c->d_counts, B);
   ALLOC(c->d_kmean, B);
   ALLOC(c->d_lnk, B);
@@ -1063,7 +1066,7 @@ int pm_nu_copy_modes(pm_nu_ctx* ctx, int box, float* out) {
   // a copy along x here and read the modes from it
   const size_t bytes = static_cast<size_t>(c->nbox) * c->MH * sizeof(float2);
   PMNU_HIP(hipMemcpyAsync(c->ck[2], c->ck[0], bytes, hipMemcpyDeviceToDevice, c->stream));
-  hipError_t e = launch_fwd_x_bin(c->N, c->ck[2], c->tw, c->bin_of_n2, nullptr, c->B, c->nbox,
+  hipError_t e = launch_fwd_x_bin(c->N, c->ck[2], c->tw, c->bin_of_n2, c->d_edges, nullptr, c->B, c->nbox,
                                   c->stream);
   if (e == hipSuccess)
     e = launch_copy_modes(c->N, c->ck[2], reinterpret_cast<float2*>(out), box, c->stream);

@@ -39,27 +39,27 @@ struct StaticTables {
 };
 
 // The density cleared by every workgroup; the first ones also write the bin of every integer
-// |n|^2 (as the context's host table) and the twiddles. One launch of N^3 / 1024 workgroups
-// (each thread clears two nodes) instead of a table kernel of one workgroup, which also
-// counted the modes there (112 us at N = 64, of 140 for the call), and two fills.
+// |n|^2 (as the context's host table), the bins' edges and the twiddles. One launch of N^3 / 1024 workgroups (each thread clears two nodes) instead of a
+// table kernel of one workgroup, which also counted the modes there (112 us at N = 64, of 140
+// for the call), and two fills.
 __global__ __launch_bounds__(512) void static_setup_kernel(StaticTables t, int n, int nbins,
-                                                           int n2max,
                                                            uint16_t* __restrict__ bin_of_n2,
+                                                           int* __restrict__ edges,
                                                            float2* __restrict__ tw,
                                                            ulonglong2* __restrict__ rho,
                                                            int64_t n_pairs) {
   const int64_t gid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (gid < n_pairs) rho[gid] = make_ulonglong2(0ull, 0ull);
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t i = gid; i <= n2max; i += stride) {
-    const int n2 = static_cast<int>(i);
+  if (gid <= nbins) edges[gid] = t.edges[gid];
+  if (gid < n) tw[gid] = t.tw[gid];
+  if (gid <= 3 * n * n / 4) {
+    const int n2 = static_cast<int>(gid);
     int lo = 0, hi = nbins - 1;        // the last b with edges[b] <= n2, at most nbins - 1
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (t.edges[mid] <= n2) lo = mid; else hi = mid - 1;
     }
     bin_of_n2[n2] = static_cast<uint16_t>(n2 == 0 ? 0 : lo);
-    if (n2 < n) tw[n2] = t.tw[n2];       // n <= n2max = 3 n^2 / 4 from n = 2 on
   }
 }
 
@@ -145,13 +145,13 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
   // layout of the scratch for this call
   const int64_t M = static_cast<int64_t>(n) * n * n;
   const int64_t MH = static_cast<int64_t>(n) * n * (n / 2 + 1);
-  const int n2max = 3 * n * n / 4;
   const int n_partial = fwd_x_partials(n);
   size_t off = 0;
   const size_t o_rho = off;     off = align256(off + M * sizeof(unsigned long long));
   const size_t o_cb = off;      off = align256(off + MH * sizeof(float2));
   const size_t o_part = off;    off = align256(off + static_cast<size_t>(n_partial) * n_kbins * sizeof(double));
-  const size_t o_bins = off;    off = align256(off + (n2max + 1) * sizeof(uint16_t));
+  const size_t o_bins = off;    off = align256(off + (3 * n * n / 4 + 1) * sizeof(uint16_t));
+  const size_t o_edges = off;   off = align256(off + (n_kbins + 1) * sizeof(int));
   const size_t o_tw = off;      off = align256(off + n * sizeof(float2));
   const size_t o_flags = off;   off = align256(off + sizeof(int));
   if (n_partial <= 0 || off > static_cast<size_t>(kStaticBytes))
@@ -166,6 +166,7 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
   auto* cb = reinterpret_cast<float2*>(s + o_cb);
   auto* part = reinterpret_cast<double*>(s + o_part);
   auto* bins = reinterpret_cast<uint16_t*>(s + o_bins);
+  auto* edges = reinterpret_cast<int*>(s + o_edges);
   auto* tw = reinterpret_cast<float2*>(s + o_tw);
   auto* flags = reinterpret_cast<int*>(s + o_flags);
 
@@ -181,16 +182,16 @@ extern "C" int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles,
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int64_t pairs = M / 2;                  // the density as pairs of 64-bit nodes
-  const int64_t threads = std::max<int64_t>(pairs, n2max + 1);
+  const int64_t threads = std::max<int64_t>(pairs, kStaticMaxBins + 1);   // the edges; M/2 > 3n^2/4
   hipLaunchKernelGGL(static_setup_kernel, dim3(static_cast<unsigned>((threads + 511) / 512)),
-                     dim3(512), 0, st, t, n, n_kbins, n2max, bins, tw,
+                     dim3(512), 0, st, t, n, n_kbins, bins, edges, tw,
                      reinterpret_cast<ulonglong2*>(rho), pairs);
   hipError_t e = hipGetLastError();
   const double scale = static_cast<double>(M) / static_cast<double>(n_particles) / kFixScale;
   const double norm = std::pow(box_size, 3) / (static_cast<double>(M) * M);
   e = e ? e : launch_deposit(pos, rho, n_particles, 1, n, n / box_size, flags, 4, 256, st);
   e = e ? e : launch_fwd_zy(n, rho, nullptr, nullptr, nullptr, 0, cb, tw, scale, 1, st);
-  e = e ? e : launch_fwd_x_bin(n, cb, tw, bins, part, n_kbins, 1, st);
+  e = e ? e : launch_fwd_x_bin(n, cb, tw, bins, edges, part, n_kbins, 1, st);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(static_power_kernel, dim3(n_kbins), dim3(256), 0, st, t, n, n_kbins, part,
                        n_partial, norm, p_cdm);

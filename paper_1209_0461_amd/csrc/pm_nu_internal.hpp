@@ -145,6 +145,7 @@ struct Ctx {
   float* force = nullptr;          // [nbox][M][3] accelerations, components interleaved
   double* bin_partial = nullptr;   // [nbox][n_partial][B]
   uint16_t* bin_of_n2 = nullptr;   // [n2max+1]
+  int* d_edges = nullptr;          // [B+1] integer |n|^2 edges of the bins
   double* d_counts = nullptr;      // [B]
   double* d_kmean = nullptr;       // [B]
   double* d_lnk = nullptr;         // [B] ln of the bin means (0 for empty bins)
@@ -288,7 +289,8 @@ hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const in
 // partial != NULL: FFT along x and the mode sums per bin, data left unchanged (the step);
 // partial == NULL: FFT along x stored in place, no sums (reading the modes out)
 hipError_t launch_fwd_x_bin(int N, float2* data, const float2* tw, const uint16_t* bin_of_n2,
-                            double* partial, int B, int nbox, hipStream_t s, int v = 0);
+                            const int* edges, double* partial, int B, int nbox, hipStream_t s,
+                            int v = 0);
 // partial bin sums per box written by launch_fwd_x_bin with tile candidate v
 int fwd_x_partials(int N, int v = 0);
 // tile of FFT pass `pass` (0 fwd_z rows, 1 fwd_y lines, 2 fwd_x columns, 3 inv_x columns,
