@@ -1117,7 +1117,15 @@ __global__ __launch_bounds__(kInvZNT) void inv_z_kernel(const float2* __restrict
   constexpr int IT = (TOTAL + NT - 1) / NT;
   __shared__ float2 lds[N * ES];
   __shared__ float2 tw[N];
-  const int y0 = blockIdx.x * TY, x = blockIdx.y, box = blockIdx.z;
+  // Each XCD takes a contiguous run of (y block, x): the pieces of a 128-byte line that
+  // workgroups with TY < 16 read lie in one L2 instead of each being fetched again, and the
+  // writes of an XCD stay in order. 512^3 (TY = 8): 795 -> 685 us, 4.1 -> 4.7 TB/s, the rate of
+  // a large copy; 256^3 (TY = 16): 84 -> 82 us. The pass is bound by this traffic alone: without
+  // its transforms it takes as long.
+  static_assert(N % 8 == 0, "whole rounds over the 8 XCDs");
+  const int logical = static_cast<int>(blockIdx.x % 8) * static_cast<int>(gridDim.x / 8) +
+                      static_cast<int>(blockIdx.x / 8);
+  const int y0 = logical % (N / TY) * TY, x = logical / (N / TY) % N, box = logical / (N / TY * N);
   load_twiddles<N, NT>(tw, twg);
   const size_t plane = ((static_cast<size_t>(box) * N + x) * NK) * N + y0;   // (k = 0, y0)
   const int pr = threadIdx.x % PAIRS;                 // row pair within the field
@@ -1470,7 +1478,7 @@ template <int N> struct InvZ {
                         const float2* tw, float kf, int nbox, hipStream_t s, int v) {
     auto go = [&](auto ty) -> hipError_t {
       constexpr int TY = decltype(ty)::value;
-      dim3 grid(N / TY, N, nbox);
+      dim3 grid(N / TY * N * nbox);
       hipLaunchKernelGGL((inv_z_kernel<N, TY>), grid, dim3(kInvZNT), 0, s, g1, g2, g3, out, tw, kf,
                          nbox);
       return hipGetLastError();
