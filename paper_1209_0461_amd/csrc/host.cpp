@@ -457,7 +457,7 @@ void free_ctx(Ctx* c) {
   for (void* p : bufs)
     if (p) hipFree(p);
   for (void* p : {static_cast<void*>(c->h_tg), static_cast<void*>(c->h_resp),
-                  static_cast<void*>(c->h_kd)})
+                  static_cast<void*>(c->h_kd), static_cast<void*>(c->h_spec)})
     if (p) hipHostFree(p);
   if (c->ev_tg) hipEventDestroy(c->ev_tg);
   if (c->ev_kd) hipEventDestroy(c->ev_kd);
@@ -600,6 +600,8 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
           hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_resp), nb * sizeof(RespBox)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_kd), 2 * nb * sizeof(double)) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&c->h_spec), (3 * B + 1) * sizeof(double)) !=
+          hipSuccess ||
       hipEventCreateWithFlags(&c->ev_tg, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&c->ev_kd, hipEventDisableTiming) != hipSuccess) {
     free_ctx(c);
@@ -986,14 +988,20 @@ int pm_nu_get_spectrum(pm_nu_ctx* ctx, int box, double* p_cdm, double* pnu_half,
                                     c->nbox, c->pcdm, c->stream);
     if (e != hipSuccess) return set_error(PM_NU_EHIP, "bin power: %s", hipGetErrorString(e));
   }
-  PMNU_HIP(hipStreamSynchronize(c->stream));
   const size_t B = c->B;
-  if (p_cdm) PMNU_HIP(hipMemcpy(p_cdm, c->pcdm + box * B, B * sizeof(double), hipMemcpyDeviceToHost));
-  if (pnu_half)
-    PMNU_HIP(hipMemcpy(pnu_half, c->pnu + box * B, B * sizeof(double), hipMemcpyDeviceToHost));
-  if (ratio) PMNU_HIP(hipMemcpy(ratio, c->ratio + box * B, B * sizeof(double), hipMemcpyDeviceToHost));
   int flags = 0;
-  PMNU_HIP(hipMemcpy(&flags, c->d_flags, sizeof(int), hipMemcpyDeviceToHost));
+  {
+    std::lock_guard<std::mutex> hold(c->spec_lock);   // readers of the same context
+    const double* h = c->h_spec;
+    hipError_t e = launch_read_spectrum(c->pcdm + box * B, c->pnu + box * B, c->ratio + box * B,
+                                        c->d_flags, c->B, c->h_spec, c->stream);
+    if (e != hipSuccess) return set_error(PM_NU_EHIP, "read spectrum: %s", hipGetErrorString(e));
+    PMNU_HIP(hipStreamSynchronize(c->stream));
+    if (p_cdm) std::copy(h, h + B, p_cdm);
+    if (pnu_half) std::copy(h + B, h + 2 * B, pnu_half);
+    if (ratio) std::copy(h + 2 * B, h + 3 * B, ratio);
+    flags = static_cast<int>(h[3 * B]);
+  }
   if (flags & 1) {
     PMNU_HIP(hipMemset(c->d_flags, 0, sizeof(int)));
     return set_error(PM_NU_ENONFINITE, "a non-finite particle position was skipped");

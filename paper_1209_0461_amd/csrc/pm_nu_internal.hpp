@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -180,6 +181,10 @@ struct Ctx {
   double* h_tg = nullptr;          // ds [nbox][qcap], then w, then log2 ds
   RespBox* h_resp = nullptr;       // [nbox]
   double* h_kd = nullptr;          // [nbox][2]
+  // where a box's spectrum is read back to: pinned, P_cdm, P_nu^{1/2}, R [3][B], d_flags; the
+  // lock is held from the launch that fills it until it has been copied to the caller
+  double* h_spec = nullptr;
+  std::mutex spec_lock;
   hipEvent_t ev_tg = nullptr, ev_kd = nullptr;
   bool density_is_delta = false;   // the last deposit wrote delta (modes 6..9), not rho
   bool keep_density = false;       // modes 8, 9: also store delta (pm_nu_set_keep_density)
@@ -380,6 +385,10 @@ hipError_t launch_kernel_values(const double* x, int64_t n, int series, double* 
                                 hipStream_t s);
 hipError_t launch_bin_power(const double* partial, int n_partial, const double* counts,
                             int nbins, double norm, int nbox, double* pcdm, hipStream_t s);
+// P_cdm, P_nu^{1/2} and R of one box (nbins each) and the flags to out, 3 nbins + 1 doubles of
+// pinned host memory
+hipError_t launch_read_spectrum(const double* pcdm, const double* pnu, const double* ratio,
+                                const int* flags, int nbins, double* out, hipStream_t s);
 hipError_t launch_ratio_index(const double* lnk, const int* nonempty, int n_nonempty,
                               int n2max, double kf, uint32_t* out, hipStream_t s);
 
