@@ -293,6 +293,23 @@ int prepare_time_grid(Ctx& c, double a_now) {
 
 namespace {
 
+// The patch deposit (mode 6) gives each 4096-particle chunk a workgroup and each coarse cell a
+// sum over its patches; with few chunks that leaves the chip idle twice, and clearing the mesh
+// and adding chunks of 512 particles to it by atomics (mode 4) is faster. A step in modes 6 and
+// 4, us, displacements of 0.3 / 2 cells: 64^3 mesh with 24^3 particles 76 / 100 and 52 / 58, 64^3
+// 60 / 67 and 53 / 58, 100^3 108 / 122 and 65 / 71; two boxes of 64^3 67 / 73 and 63 / 70, four
+// of 40^3 particles 90 / 117 and 65 / 114, of 64^3 76 / 88 and 77 / 86; a 128^3 mesh with 64^3
+// particles 135 / 170 and 130 / 157, 80^3 104 / 120 and 108 / 208. So mode 4 up to 64 chunks on
+// meshes up to 128^3 nodes, and up to 256 on meshes up to two boxes of 64^3; and always where
+// one coarse cell would cover the mesh (N < 64).
+int default_deposit_mode(int n, int nbox, int64_t np) {
+  if (n < 64) return 4;
+  const int64_t nodes = static_cast<int64_t>(n) * n * n * nbox, chunks = patch_chunks(np) * nbox;
+  const bool few = (chunks <= 64 && nodes <= 128 * 128 * 128) ||
+                   (chunks <= 256 && nodes <= 2 * 64 * 64 * 64);
+  return few ? 4 : 6;
+}
+
 int do_deposit(Ctx& c, const float* pos) {
   if (!pos) return set_error(PM_NU_EINVAL, "pos is NULL");
   const int64_t cells = c.M * c.nbox;
@@ -529,8 +546,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   int max_partial = c->n_partial;
   for (int v = 1; v < 3; ++v) max_partial = std::max(max_partial, fwd_x_partials(c->N, v));
   c->n_partial_cap = max_partial;
-  // the patch deposit is the faster one once the mesh holds many coarse cells
-  c->tune.deposit_mode = c->N >= 64 ? 6 : 4;
+  c->tune.deposit_mode = default_deposit_mode(c->N, c->nbox, c->Np);
   c->stream = static_cast<hipStream_t>(cfg->stream);
   c->m_nu.assign(m_nu_total, m_nu_total + c->nbox);
   for (int b = 0; b < c->nbox; ++b) {
