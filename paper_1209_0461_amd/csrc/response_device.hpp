@@ -138,6 +138,30 @@ __device__ __forceinline__ double2 block_sum_d2(double2 v, double* red) {
   return s;
 }
 
+// Three sums over the workgroup at once; every thread gets them. red: 3 * NT / 64 doubles.
+template <int NT>
+__device__ __forceinline__ double3 block_sum_d3(double3 v, double* red) {
+  v.x = wave_sum_d(v.x);
+  v.y = wave_sum_d(v.y);
+  v.z = wave_sum_d(v.z);
+  if constexpr (NT == 64) return v;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) {
+    red[3 * wave] = v.x;
+    red[3 * wave + 1] = v.y;
+    red[3 * wave + 2] = v.z;
+  }
+  __syncthreads();
+  double3 s = make_double3(0.0, 0.0, 0.0);
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) {
+    s.x += red[3 * w];
+    s.y += red[3 * w + 1];
+    s.z += red[3 * w + 2];
+  }
+  return s;
+}
+
 // sum over the per-workgroup partial mode sums of bin b ([box][bin][workgroup]):
 // sum w |delta_k|^2
 template <int NT = RT>
@@ -179,14 +203,12 @@ __device__ __forceinline__ double bin_mode_sum(const double* partial, int n_part
 // term is evaluated by the first wave only and enters the sum through thread 0. Each
 // thread takes ceil(nq / NT) sub-nodes q = tid + NT u, in as few rounds of at most U
 // whose loads go out together as cover them.
-// red: 2 * NT / 64 doubles.
+// exact_sums: this thread's share of the known part (x) and of the coefficient of A_n (y).
 template <int NSP, bool SERIES, int NT>   // species: 1 (equal masses) or kMaxSpecies
-__device__ __forceinline__ double exact_pnu_n(const RespBox& bx, double k, double pcdm_half,
-                                              double pnu_prev, const double* ic_pnu,
+__device__ __forceinline__ double2 exact_sums(const RespBox& bx, double k, const double* ic_pnu,
                                               double ic_theta, const double* hpm, int nbins,
                                               int b, const double* ds, const double* l2ds,
-                                              const double* w, int q_sub, int iterations,
-                                              double* red) {
+                                              const double* w, int q_sub) {
   const double inv_q = 1.0 / q_sub;
   // log2(k T/m_s) of each species: with log2(ds) per sub-node (host FP64) it gives the
   // fit's log2 x without a logarithm per sub-node
@@ -206,7 +228,7 @@ __device__ __forceinline__ double exact_pnu_n(const RespBox& bx, double k, doubl
     ic *= 1.0 - bx.ds_ic * bx.a_i * ic_theta;
     if (threadIdx.x == 0) known = ic;
   }
-  constexpr int U = NT == 64 ? 5 : 8;        // one wave: keep registers for occupancy
+  constexpr int U = 4;
   const int per = (bx.nq + NT - 1) / NT;
   const int rounds = (per + U - 1) / U;
   const int chunk = rounds > 0 ? (per + rounds - 1) / rounds : 0;
@@ -246,7 +268,11 @@ __device__ __forceinline__ double exact_pnu_n(const RespBox& bx, double k, doubl
       coef += g * cur;
     }
   }
-  const double2 sums = block_sum_d2<NT>(make_double2(known, coef), red);
+  return make_double2(known, coef);
+}
+// the iterations of Appendix B from the workgroup's sums
+__device__ __forceinline__ double exact_iterate(const RespBox& bx, double2 sums, double pcdm_half,
+                                                double pnu_prev, int iterations) {
   double pnu_guess = pnu_prev, pnu = 0.0;
   for (int it = 0; it < iterations; ++it) {
     const double a_cur = (1.0 - bx.f_nu) * pcdm_half + bx.f_nu * pnu_guess;
@@ -256,18 +282,17 @@ __device__ __forceinline__ double exact_pnu_n(const RespBox& bx, double k, doubl
   return pnu;
 }
 
-// One kernel form (I(x) series or fit, one or several species): a kernel that takes only
-// this form needs the registers of this form alone.
-template <int NT, bool SERIES, int NSP>
-__device__ __forceinline__ double exact_pnu_form(const RespBox& bx, double k, double pcdm_half,
-                                                 double pnu_prev, const double* ic_pnu,
-                                                 double ic_theta, const double* hpm, int nbins,
-                                                 int b, const double* ds, const double* l2ds,
-                                                 const double* w, int q_sub, int iterations,
-                                                 double* red) {
-  if (bx.n_sp <= 0) return 0.0;          // no massive neutrinos: the term drops out
-  return exact_pnu_n<NSP, SERIES, NT>(bx, k, pcdm_half, pnu_prev, ic_pnu, ic_theta, hpm, nbins,
-                                      b, ds, l2ds, w, q_sub, iterations, red);
+// red: 2 * NT / 64 doubles
+template <int NSP, bool SERIES, int NT>
+__device__ __forceinline__ double exact_pnu_n(const RespBox& bx, double k, double pcdm_half,
+                                              double pnu_prev, const double* ic_pnu,
+                                              double ic_theta, const double* hpm, int nbins,
+                                              int b, const double* ds, const double* l2ds,
+                                              const double* w, int q_sub, int iterations,
+                                              double* red) {
+  const double2 part = exact_sums<NSP, SERIES, NT>(bx, k, ic_pnu, ic_theta, hpm, nbins, b, ds,
+                                                   l2ds, w, q_sub);
+  return exact_iterate(bx, block_sum_d2<NT>(part, red), pcdm_half, pnu_prev, iterations);
 }
 
 template <int NT = RT>

@@ -42,46 +42,71 @@ __global__ __launch_bounds__(NT) void response_kernel(
     const double* __restrict__ tg_w, int nbins, int jcap,
     int qcap, int q_sub, int iterations, double norm, double* __restrict__ pcdm_out,
     double* __restrict__ pnu_out, double* __restrict__ ratio_out) {
-  __shared__ double red[2 * NT / 64];
+  __shared__ double red[3 * NT / 64];
   const int b = blockIdx.x, box = blockIdx.y;
   const RespBox bx = boxes[box];
   const size_t ob = static_cast<size_t>(box) * nbins + b;
   double* hpm = hist_pm + static_cast<size_t>(box) * jcap * nbins;
   double* hpn = hist_pnu + static_cast<size_t>(box) * jcap * nbins;
-
-  // 1. binned CDM power
-  const double s = bin_mode_sum<NT>(partial, n_partial, nbins, box, b, red);
   const double cb = counts[b];
+  const size_t row = static_cast<size_t>(bx.n_cur) * nbins + b;
   if (!(cb > 0.0)) {
     if (threadIdx.x == 0) {
-      pcdm_out[ob] = 0.0;
-      pnu_out[ob] = 0.0;
-      ratio_out[ob] = 0.0;
-      hpm[static_cast<size_t>(bx.n_cur) * nbins + b] = 0.0;
-      hpn[static_cast<size_t>(bx.n_cur) * nbins + b] = 0.0;
+      pcdm_out[ob] = pnu_out[ob] = ratio_out[ob] = 0.0;
+      hpm[row] = hpn[row] = 0.0;
     }
     return;
   }
-  const double pcdm = norm * s / cb;
-  const double pcdm_half = sqrt(pcdm);
+
+  // 1. the bin's partial mode sums: the first U of this thread go out here and are added up
+  // after the history integral, which does not depend on them
+  constexpr int U = NT == 64 ? 4 : 16;
+  const double* pp = partial + (static_cast<size_t>(box) * nbins + b) * n_partial;
+  double v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = threadIdx.x + u * NT;
+    v[u] = i < n_partial ? pp[i] : 0.0;
+  }
+  const double k = kmean[b], theta = ic_theta[ob];
+  const double pnu_prev = bx.n_cur > 0 ? hpn[row - nbins] : 0.0;
 
   // 2. history integral
   constexpr bool SERIES = FORM >= 2;
   constexpr int NSP = (FORM & 1) ? kMaxSpecies : 1;
-  const double pnu = exact_pnu_form<NT, SERIES, NSP>(bx, kmean[b], pcdm_half,
-                               (bx.n_cur > 0 ? hpn[static_cast<size_t>(bx.n_cur - 1) * nbins + b] : 0.0),
-                               ic_pnu + static_cast<size_t>(box) * kMaxSpecies * nbins,
-                               ic_theta[ob], hpm, nbins, b, tg_ds + static_cast<size_t>(box) * qcap,
-                               tg_l2 + static_cast<size_t>(box) * qcap,
-                               tg_w + static_cast<size_t>(box) * qcap, q_sub, iterations, red);
-  if (threadIdx.x == 0) {
-    pcdm_out[ob] = pcdm;
-    pnu_out[ob] = pnu;
-    // a bin without CDM power has no phase to carry the neutrinos (eq. (phases)): R = 0
-    ratio_out[ob] = pcdm_half > 0.0 ? pnu / pcdm_half : 0.0;
-    hpm[static_cast<size_t>(bx.n_cur) * nbins + b] = (1.0 - bx.f_nu) * pcdm_half + bx.f_nu * pnu;
-    hpn[static_cast<size_t>(bx.n_cur) * nbins + b] = pnu;
+  double2 h = make_double2(0.0, 0.0);
+  if (bx.n_sp > 0)                       // no massive neutrinos: the term drops out
+    h = exact_sums<NSP, SERIES, NT>(bx, k, ic_pnu + static_cast<size_t>(box) * kMaxSpecies * nbins,
+                                    theta, hpm, nbins, b, tg_ds + static_cast<size_t>(box) * qcap,
+                                    tg_l2 + static_cast<size_t>(box) * qcap,
+                                    tg_w + static_cast<size_t>(box) * qcap, q_sub);
+  double s = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) s += v[u];
+  for (int i0 = U * NT; i0 < n_partial; i0 += U * NT) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + threadIdx.x + u * NT;
+      v[u] = i < n_partial ? pp[i] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) s += v[u];
   }
+  const double3 sums = block_sum_d3<NT>(make_double3(h.x, h.y, s), red);
+
+  // 3. P_cdm, the iterations, R and the history row
+  if (threadIdx.x != 0) return;
+  const double pcdm = norm * sums.z / cb;
+  const double pcdm_half = sqrt(pcdm);
+  const double pnu = bx.n_sp > 0 ? exact_iterate(bx, make_double2(sums.x, sums.y), pcdm_half,
+                                                 pnu_prev, iterations)
+                                 : 0.0;
+  pcdm_out[ob] = pcdm;
+  pnu_out[ob] = pnu;
+  // a bin without CDM power has no phase to carry the neutrinos (eq. (phases)): R = 0
+  ratio_out[ob] = pcdm_half > 0.0 ? pnu / pcdm_half : 0.0;
+  hpm[row] = (1.0 - bx.f_nu) * pcdm_half + bx.f_nu * pnu;
+  hpn[row] = pnu;
 }
 
 // The exact response for many (bin, box) pairs with the fit and one species per box (the
