@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <limits>
 #include <numeric>
@@ -160,6 +161,15 @@ int nodes_for(const Ctx& c, int box, double a_now, std::vector<double>& nodes, i
   return PM_NU_OK;
 }
 
+// Until the staging's last upload has run. The upload itself says so (launch_upload); if it has
+// not for a tenth of a second, waiting for the stream also gives back the error of one that failed.
+hipError_t wait_upload(const Ctx& c) {
+  const auto give_up = std::chrono::steady_clock::now() + std::chrono::milliseconds(100);
+  while (__atomic_load_n(c.h_up, __ATOMIC_ACQUIRE) != c.up_seq)
+    if (std::chrono::steady_clock::now() > give_up) return hipStreamSynchronize(c.stream);
+  return hipSuccess;
+}
+
 // Time grid of eq. (P-final) for every box at a_now (host FP64). The sub-intervals between
 // stored nodes are kept per box and only the newest interval, to a_now, is integrated
 // afresh; the arrays go to the device by stream-ordered copies from pinned staging.
@@ -176,7 +186,7 @@ int prepare_time_grid(Ctx& c, double a_now) {
   const double pref = 1.5 * om * kH0 * kH0;   // the source keeps all matter, Omega_M
   const int Q = c.Q;
   const size_t qcap = static_cast<size_t>(c.qcap);
-  PMNU_HIP(hipEventSynchronize(c.ev_tg));     // the staging's previous upload has run
+  PMNU_HIP(wait_upload(c));
   double* ds_all = c.h_tg;
   double* w_all = c.h_tg + c.nbox * qcap;
   double* l2_all = c.h_tg + 2 * c.nbox * qcap;
@@ -266,13 +276,12 @@ int prepare_time_grid(Ctx& c, double a_now) {
       }
     }
   }
-  const size_t bytes = c.nbox * qcap * sizeof(double);
-  PMNU_HIP(hipMemcpyAsync(c.tg_ds, ds_all, bytes, hipMemcpyHostToDevice, c.stream));
-  PMNU_HIP(hipMemcpyAsync(c.tg_w, w_all, bytes, hipMemcpyHostToDevice, c.stream));
-  PMNU_HIP(hipMemcpyAsync(c.tg_l2, l2_all, bytes, hipMemcpyHostToDevice, c.stream));
-  PMNU_HIP(hipMemcpyAsync(c.d_resp, c.h_resp, c.nbox * sizeof(RespBox), hipMemcpyHostToDevice,
-                          c.stream));
-  PMNU_HIP(hipEventRecord(c.ev_tg, c.stream));
+  int nq_max = 0;
+  for (int b = 0; b < c.nbox; ++b) nq_max = std::max(nq_max, c.h_resp[b].nq);
+  PMNU_HIP(launch_upload(c.h_tg, c.tg_ds, c.tg_w, c.tg_l2, c.nbox, static_cast<int>(qcap), nq_max,
+                         c.h_resp, c.d_resp, c.h_kd, c.d_kd, c.kd_staged ? 2 * c.nbox : 0,
+                         c.d_up, c.h_up, ++c.up_seq, c.stream));
+  c.kd_staged = false;
   c.tg_a_now = a_now;
   c.tg_version = c.hist_version;
   c.n_cur = ncur;
@@ -470,14 +479,13 @@ void free_ctx(Ctx* c) {
                   c->ratio, c->hist_pm, c->hist_pnu, c->ic_pnu, c->ic_theta, c->tg_ds,
                   c->tg_l2, c->tg_w, c->d_resp, c->ridx, c->d_next, c->tw, c->inv_w2,
                   c->d_flags, c->patches, c->reg_count, c->reg_list, c->rho_fb, c->n_fb,
-                  c->delta, c->d_kd};
+                  c->delta, c->d_kd, c->d_up};
   for (void* p : bufs)
     if (p) hipFree(p);
   for (void* p : {static_cast<void*>(c->h_tg), static_cast<void*>(c->h_resp),
-                  static_cast<void*>(c->h_kd), static_cast<void*>(c->h_spec)})
+                  static_cast<void*>(c->h_kd), static_cast<void*>(c->h_spec),
+                  static_cast<void*>(c->h_up)})
     if (p) hipHostFree(p);
-  if (c->ev_tg) hipEventDestroy(c->ev_tg);
-  if (c->ev_kd) hipEventDestroy(c->ev_kd);
   delete c;
 }
 
@@ -611,6 +619,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
     ALLOC(c->delta, nb * c->M);
   }
   ALLOC(c->d_kd, 2 * nb);
+  ALLOC(c->d_up, 1);
 #undef ALLOC
   if (hipHostMalloc(reinterpret_cast<void**>(&c->h_tg), 3 * nb * c->qcap * sizeof(double)) !=
           hipSuccess ||
@@ -618,12 +627,12 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
       hipHostMalloc(reinterpret_cast<void**>(&c->h_kd), 2 * nb * sizeof(double)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_spec), (3 * B + 1) * sizeof(double)) !=
           hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_tg, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&c->ev_kd, hipEventDisableTiming) != hipSuccess) {
+      hipHostMalloc(reinterpret_cast<void**>(&c->h_up), sizeof(uint32_t)) != hipSuccess) {
     free_ctx(c);
-    return set_error(PM_NU_ENOMEM, "pinned staging or events could not be created");
+    return set_error(PM_NU_ENOMEM, "pinned staging could not be allocated");
   }
   std::memset(c->h_tg, 0, 3 * nb * c->qcap * sizeof(double));
+  *c->h_up = 0;
   c->tgc.resize(c->nbox);
   build_bins(*c);
   if (c->nonempty.empty()) {
@@ -669,6 +678,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   e = e ? e : hipMemset(c->reg_count, 0, nb * patch_coarse_cells(c->N) * sizeof(int));
   e = e ? e : hipMemset(c->rho_fb, 0, nb * c->M * sizeof(unsigned long long));
   e = e ? e : hipMemset(c->n_fb, 0, 2 * sizeof(int));
+  e = e ? e : hipMemset(c->d_up, 0, sizeof(int));
   e = e ? e : hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_ctx(c);
@@ -914,14 +924,19 @@ int pm_nu_step(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now) {
 
 namespace {
 
-// Kick and drift factors of every box, copied in stream order ahead of the next kick_drift
-// launch.
-int upload_kd(Ctx& c, const std::vector<double>& kd) {
-  PMNU_HIP(hipEventSynchronize(c.ev_kd));     // the staging's previous upload has run
+// Kick and drift factors of every box to their staging; they go up with the next time grid, or
+// by upload_kd.
+int stage_kd(Ctx& c, const std::vector<double>& kd) {
+  PMNU_HIP(wait_upload(c));
   std::copy(kd.begin(), kd.end(), c.h_kd);
-  PMNU_HIP(hipMemcpyAsync(c.d_kd, c.h_kd, kd.size() * sizeof(double), hipMemcpyHostToDevice,
-                          c.stream));
-  PMNU_HIP(hipEventRecord(c.ev_kd, c.stream));
+  c.kd_staged = true;
+  return PM_NU_OK;
+}
+int upload_kd(Ctx& c) {
+  if (!c.kd_staged) return PM_NU_OK;
+  c.kd_staged = false;
+  PMNU_HIP(launch_upload(c.h_tg, c.tg_ds, c.tg_w, c.tg_l2, c.nbox, c.qcap, 0, c.h_resp, c.d_resp,
+                         c.h_kd, c.d_kd, 2 * c.nbox, c.d_up, c.h_up, ++c.up_seq, c.stream));
   return PM_NU_OK;
 }
 
@@ -961,16 +976,13 @@ int pm_nu_advance(pm_nu_ctx* ctx, float* pos, float* vel, float* acc, const doub
     kd[2 * b] = a_steps[0] * kick_of(bg[b], a_steps[0], a_mid(0));
     kd[2 * b + 1] = ds_of(bg[b], a_steps[0], a_steps[1]);
   }
-  int rc = upload_kd(*c, kd);
+  int rc = stage_kd(*c, kd);
+  if (!rc) rc = upload_kd(*c);
   if (rc) return rc;
   TIMED(*c, ST_KICK_DRIFT, launch_kick_drift(pos, vel, acc, c->d_kd, c->Np, c->nbox, L, true,
                                              c->stream));
   for (int j = 0; j < n_steps; ++j) {
     const double a1 = a_steps[j + 1];
-    rc = do_deposit(*c, pos);
-    if (rc) return rc;
-    rc = do_response_mode(*c, a1, c->cfg.response_mode);
-    if (rc) return rc;
     // the interpolation applies the force at a1 at once: the closing half kick of this step
     // with the opening one of the next and the next drift, or (last step) the closing half
     // kick alone, storing the force
@@ -979,7 +991,13 @@ int pm_nu_advance(pm_nu_ctx* ctx, float* pos, float* vel, float* acc, const doub
       kd[2 * b] = a1 * kick_of(bg[b], a_mid(j), last ? a1 : a_mid(j + 1));
       kd[2 * b + 1] = last ? 0.0 : ds_of(bg[b], a1, a_steps[j + 2]);
     }
-    rc = upload_kd(*c, kd);
+    // ahead of the deposit, so that the host has a whole step of the device for the next grid
+    rc = stage_kd(*c, kd);
+    if (!rc) rc = prepare_time_grid(*c, a1);
+    if (!rc) rc = upload_kd(*c);
+    c->kd_staged = false;
+    if (!rc) rc = do_deposit(*c, pos);
+    if (!rc) rc = do_response_mode(*c, a1, c->cfg.response_mode);
     if (rc) return rc;
     Leap lp;
     lp.vel = vel;

@@ -185,7 +185,12 @@ struct Ctx {
   // lock is held from the launch that fills it until it has been copied to the caller
   double* h_spec = nullptr;
   std::mutex spec_lock;
-  hipEvent_t ev_tg = nullptr, ev_kd = nullptr;
+  // uploads from the staging launched so far, the one that has last run (pinned, written by
+  // the upload itself) and its count of finished workgroups
+  uint32_t up_seq = 0;
+  uint32_t* h_up = nullptr;
+  int* d_up = nullptr;
+  bool kd_staged = false;          // h_kd goes up with the next time grid
   bool density_is_delta = false;   // the last deposit wrote delta (modes 6..9), not rho
   bool keep_density = false;       // modes 8, 9: also store delta (pm_nu_set_keep_density)
   bool density_kept = false;       // the last deposit left a readable density
@@ -385,6 +390,14 @@ hipError_t launch_kernel_values(const double* x, int64_t n, int series, double* 
                                 hipStream_t s);
 hipError_t launch_bin_power(const double* partial, int n_partial, const double* counts,
                             int nbins, double norm, int nbox, double* pcdm, hipStream_t s);
+// The host-built arrays from their pinned staging to the device: with nq > 0 the first nq
+// sub-nodes of the time grid of every box (h_tg: ds, w, log2 ds [nbox][qcap] each) and the
+// response's constants, with n_kd > 0 the kick and drift factors; the last workgroup to end
+// (counted in d_up, zero between launches) then writes seq to h_up, in pinned memory
+hipError_t launch_upload(const double* h_tg, double* tg_ds, double* tg_w, double* tg_l2, int nbox,
+                         int qcap, int nq, const RespBox* h_resp, RespBox* d_resp,
+                         const double* h_kd, double* d_kd, int n_kd, int* d_up, uint32_t* h_up,
+                         uint32_t seq, hipStream_t s);
 // P_cdm, P_nu^{1/2} and R of one box (nbins each) and the flags to out, 3 nbins + 1 doubles of
 // pinned host memory
 hipError_t launch_read_spectrum(const double* pcdm, const double* pnu, const double* ratio,

@@ -25,6 +25,8 @@
 // packed in 32 bits, so that R(|k|) is linear in ln k between the means of the non-empty
 // bins and held at the end values outside them; the first inverse pass turns it and the
 // step's R into T(n^2) = (1 - f_nu) + f_nu R(|k|) (eq. (phases)).
+#include <algorithm>
+
 #include "response_device.hpp"
 
 namespace pmnu {
@@ -263,6 +265,60 @@ __global__ __launch_bounds__(RT) void bin_power_kernel(const double* __restrict_
     pcdm_out[static_cast<size_t>(box) * nbins + b] = counts[b] > 0.0 ? norm * s / counts[b] : 0.0;
 }
 
+// The time grid, the response's constants and the leapfrog's factors, read from pinned host
+// memory by one kernel: five copies a step of the stepping loop, each a dispatch of its own
+// between barriers, left the device idle for 20 us a step (8 steps of a 128^3 box 1312 -> 1174).
+// Every thread has four loads in flight (they cross PCIe). The host must not write the staging
+// again before it has been read: the last workgroup to end says so in pinned memory, since an
+// event recorded here would hold the next kernel back by 5 us.
+__global__ __launch_bounds__(256) void upload_kernel(const double* __restrict__ h_tg,
+                                                     double* __restrict__ tg_ds,
+                                                     double* __restrict__ tg_w,
+                                                     double* __restrict__ tg_l2, int nbox,
+                                                     int qcap, int nq,
+                                                     const double* __restrict__ h_resp,
+                                                     double* __restrict__ d_resp, int resp_words,
+                                                     const double* __restrict__ h_kd,
+                                                     double* __restrict__ d_kd, int n_kd,
+                                                     int* d_up, uint32_t* h_up, uint32_t seq) {
+  const int64_t grid = static_cast<int64_t>(nbox) * nq;
+  const int64_t total = 3 * grid + resp_words + n_kd;
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+  constexpr int U = 4;
+  for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i0 < total;
+       i0 += U * stride) {
+    double v[U];
+    double* dst[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * stride;
+      const double* src = nullptr;
+      dst[u] = nullptr;
+      if (i < 3 * grid) {
+        const int which = static_cast<int>(i / grid);   // grid > 0 here
+        const int64_t j = i - which * grid, o = j / nq * qcap + j % nq;
+        src = h_tg + which * static_cast<int64_t>(nbox) * qcap + o;
+        dst[u] = (which == 0 ? tg_ds : which == 1 ? tg_w : tg_l2) + o;
+      } else if (i < 3 * grid + resp_words) {
+        src = h_resp + (i - 3 * grid);
+        dst[u] = d_resp + (i - 3 * grid);
+      } else if (i < total) {
+        src = h_kd + (i - 3 * grid - resp_words);
+        dst[u] = d_kd + (i - 3 * grid - resp_words);
+      }
+      v[u] = src ? *src : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (dst[u]) *dst[u] = v[u];
+  }
+  __syncthreads();                                  // every load of the workgroup has returned
+  if (threadIdx.x == 0 && atomicAdd(d_up, 1) == static_cast<int>(gridDim.x) - 1) {
+    *d_up = 0;
+    __hip_atomic_store(h_up, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
 // A box's spectrum and the flags to pinned host memory: one workgroup, one launch and one wait
 // where four blocking copies each waited for the device (16 boxes x 128 bins read one after the
 // other: 61 -> 18 us each).
@@ -394,6 +450,20 @@ hipError_t launch_bin_power(const double* partial, int n_partial, const double* 
                             int nbins, double norm, int nbox, double* pcdm, hipStream_t s) {
   hipLaunchKernelGGL(bin_power_kernel, dim3(nbins, nbox), dim3(RT), 0, s, partial, n_partial,
                      counts, nbins, norm, pcdm);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const double* h_tg, double* tg_ds, double* tg_w, double* tg_l2, int nbox,
+                         int qcap, int nq, const RespBox* h_resp, RespBox* d_resp,
+                         const double* h_kd, double* d_kd, int n_kd, int* d_up, uint32_t* h_up,
+                         uint32_t seq, hipStream_t s) {
+  static_assert(sizeof(RespBox) % sizeof(double) == 0, "copied in words of 8 bytes");
+  const int words = nq > 0 ? static_cast<int>(nbox * sizeof(RespBox) / sizeof(double)) : 0;
+  const int64_t total = 3 * static_cast<int64_t>(nbox) * nq + words + n_kd;
+  const int blocks = static_cast<int>(std::min<int64_t>((total + 1023) / 1024, 256));
+  hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(256), 0, s, h_tg, tg_ds, tg_w, tg_l2, nbox,
+                     qcap, nq, reinterpret_cast<const double*>(h_resp),
+                     reinterpret_cast<double*>(d_resp), words, h_kd, d_kd, n_kd, d_up, h_up, seq);
   return hipGetLastError();
 }
 
