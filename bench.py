@@ -115,7 +115,7 @@ def kernel_name(stage, tuning, n_mesh):
     if stage == "inv_xy_green":
         return "inv_xy_kernel<%d>" % n_mesh
     if stage == "inv_yz":
-        return "inv_yz_kernel<%d>" % n_mesh
+        return "inv_yz_kernel<%d, 3>" % n_mesh      # many boxes; <N, 1> up to 256 planes
     if stage == "patch_fwd_z":
         return "patch_fwd_z_kernel<%d>" % n_mesh
     if stage == "fft_fwd_zy":

@@ -1192,8 +1192,12 @@ __global__ __launch_bounds__(kInvZNT) void inv_z_kernel(const float2* __restrict
 // two rows per complex line as A + iB, -i k_z on G1) and are transformed along z into the
 // plane's interleaved accelerations. The same arithmetic in the same order as the two passes,
 // so the same forces bit for bit; G1..G3 never reach HBM.
+//
+// NC = 1: one workgroup per (x-plane, box, component) transforms only the field of its
+// component (grid.z; the three of a plane on one XCD, whose L2 joins their interleaved writes),
+// where the planes alone would leave most of the chip idle (kSplitPlanes).
 constexpr int kInvYZNT = 512;   // threads per workgroup of inv_yz_kernel
-template <int N>
+template <int N, int NC>
 __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restrict__ f1,
                                                           const float2* __restrict__ f2,
                                                           float* __restrict__ out,
@@ -1201,15 +1205,16 @@ __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restri
                                                           float kf) {
   constexpr int NT = kInvYZNT;                     // this kernel's workgroup size
   constexpr int NK = Shape<N>::NK;
-  constexpr int NL1 = 3 * NK, ES1 = NL1 + 1;       // y lines: F1, -i k_y F1, F2 per k_z
-  constexpr int NL2 = 3 * N / 2, ES2 = NL2 + 1;    // z lines: row pairs of rows comp N + y
+  constexpr int NL1 = NC * NK, ES1 = NL1 + 1;      // y lines: F1, -i k_y F1, F2 per k_z
+  constexpr int NL2 = NC * N / 2, ES2 = NL2 + 1;   // z lines: row pairs of rows comp N + y
   constexpr int LDS_N = N * (ES1 > ES2 ? ES1 : ES2);
-  constexpr int NG = 3 * NK * N;                   // G values of the plane
+  constexpr int NG = NC * NK * N;                  // G values of the plane
   constexpr int PER = (NG + NT - 1) / NT;
   static_assert(N <= 64, "the plane's modes must fit the LDS");
   __shared__ float2 lds[LDS_N];
   __shared__ float2 tw[N];
   const int x = blockIdx.x, box = blockIdx.y, tid = threadIdx.x;
+  const int comp0 = NC == 1 ? blockIdx.z : 0;      // NC = 1: this workgroup's component
   load_twiddles<N, NT>(tw, twg);
   // 1. F1, F2 of the plane: the k_z rows of [box][k_z][x][k_y], two values per float4
   {
@@ -1221,8 +1226,8 @@ __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restri
       if (t < NK * N / 2) {
         const int kz = t / (N / 2), e0 = 2 * (t % (N / 2));
         const size_t o = ((static_cast<size_t>(box) * NK + kz) * N + x) * N + e0;
-        va[i] = *reinterpret_cast<const float4*>(f1 + o);
-        vb[i] = *reinterpret_cast<const float4*>(f2 + o);
+        if (NC == 3 || comp0 != 0) va[i] = *reinterpret_cast<const float4*>(f1 + o);
+        if (NC == 3 || comp0 == 0) vb[i] = *reinterpret_cast<const float4*>(f2 + o);
       }
     }
 #pragma unroll
@@ -1235,10 +1240,16 @@ __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restri
       for (int h = 0; h < 2; ++h) {
         const int e = e0 + h;
         const float2 a = h ? make_float2(a4.z, a4.w) : make_float2(a4.x, a4.y);
-        lds[e * ES1 + kz] = a;
+        const float2 f = h ? make_float2(b4.z, b4.w) : make_float2(b4.x, b4.y);
         const float ky = (e == N / 2) ? 0.f : kf * static_cast<float>(signed_index(e, N));
-        lds[e * ES1 + NK + kz] = make_float2(ky * a.y, -ky * a.x);     // -i k_y F1
-        lds[e * ES1 + 2 * NK + kz] = h ? make_float2(b4.z, b4.w) : make_float2(b4.x, b4.y);
+        const float2 d = make_float2(ky * a.y, -ky * a.x);             // -i k_y F1
+        if constexpr (NC == 3) {
+          lds[e * ES1 + kz] = a;
+          lds[e * ES1 + NK + kz] = d;
+          lds[e * ES1 + 2 * NK + kz] = f;
+        } else {
+          lds[e * ES1 + kz] = comp0 == 0 ? f : comp0 == 1 ? d : a;
+        }
       }
     }
   }
@@ -1264,13 +1275,13 @@ __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restri
     const int t = tid + i * NT;
     if (t >= NG) break;
     const int y = t % N, r = t / N, k = r % NK, f = r / NK;
-    const int comp = 2 - f;
+    const int comp = NC == 1 ? comp0 : 2 - f;
     float2 a = g[i];
     if (comp == 2) {                                 // -i k_z G1
       const float kz = (k == N / 2) ? 0.f : kf * static_cast<float>(k);
       a = make_float2(kz * a.y, -kz * a.x);
     }
-    const int row = comp * N + y, p = row >> 1;
+    const int row = (NC == 1 ? 0 : comp * N) + y, p = row >> 1;
     if (k == 0 || k == N / 2)
       ldsf[(k * ES2 + p) * 2 + (row & 1)] = a.x;
     else if ((row & 1) == 0)
@@ -1292,9 +1303,9 @@ __global__ __launch_bounds__(kInvYZNT) void inv_yz_kernel(const float2* __restri
   for (int n = tid; n < N * N; n += NT) {
     const int y = n / N, z = n % N;
 #pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-      const int row = comp * N + y;
-      dst[3 * n + comp] = ldsf[(z * ES2 + (row >> 1)) * 2 + (row & 1)];
+    for (int c = 0; c < NC; ++c) {
+      const int row = c * N + y;
+      dst[3 * n + comp0 + c] = ldsf[(z * ES2 + (row >> 1)) * 2 + (row & 1)];
     }
   }
 }
@@ -1461,14 +1472,22 @@ template <int N> struct InvXY {
     }
   }
 };
+// Up to this many planes a workgroup takes one component of a plane, not all three. us with one
+// / three components a workgroup (6.4 of them an empty launch): one 32^3 box 6.4 / 7.0, eight
+// 7.8 / 8.1, one 64^3 box 9.7 / 13.3, two 10.8 / 13.3, four 12.7 / 14.0, eight 25.1 / 20.0.
+constexpr int kSplitPlanes = 256;
 template <int N> struct InvYZ {
   static hipError_t run(const float2* f1, const float2* f2, float* out, const float2* tw, float kf,
                         int nbox, hipStream_t s) {
     if constexpr (N > 64) {
       return hipErrorInvalidValue;                 // the plane's modes do not fit the LDS
     } else {
-      hipLaunchKernelGGL(inv_yz_kernel<N>, dim3(N, nbox), dim3(kInvYZNT), 0, s, f1, f2, out, tw,
-                         kf);
+      if (N * nbox <= kSplitPlanes)
+        hipLaunchKernelGGL((inv_yz_kernel<N, 1>), dim3(N, nbox, 3), dim3(kInvYZNT), 0, s, f1, f2,
+                           out, tw, kf);
+      else
+        hipLaunchKernelGGL((inv_yz_kernel<N, 3>), dim3(N, nbox), dim3(kInvYZNT), 0, s, f1, f2, out,
+                           tw, kf);
       return hipGetLastError();
     }
   }
