@@ -1072,14 +1072,6 @@ __global__ __launch_bounds__(256, CH <= 1024 ? 6 : 1) void interp_tiled_kernel(c
   }
 }
 
-__global__ void fixed_to_float_kernel(const unsigned long long* __restrict__ src,
-                                      float* __restrict__ dst, int64_t n) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n;
-       i += stride)
-    dst[i] = static_cast<float>(static_cast<double>(src[i]) / kFixScale);
-}
-
 __global__ void extract_component_kernel(const float* __restrict__ src, float* __restrict__ dst,
                                          int64_t n, int comp) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -1115,13 +1107,6 @@ hipError_t launch_extract_component(const float* src, float* dst, int64_t n, int
                                    hipStream_t s) {
   int blocks = static_cast<int>(std::min<int64_t>((n + 255) / 256, 8192));
   hipLaunchKernelGGL(extract_component_kernel, dim3(blocks), dim3(256), 0, s, src, dst, n, comp);
-  return hipGetLastError();
-}
-
-hipError_t launch_fixed_to_float(const unsigned long long* src, float* dst, int64_t n,
-                                 hipStream_t s) {
-  int blocks = static_cast<int>(std::min<int64_t>((n + 255) / 256, 8192));
-  hipLaunchKernelGGL(fixed_to_float_kernel, dim3(blocks), dim3(256), 0, s, src, dst, n);
   return hipGetLastError();
 }
 

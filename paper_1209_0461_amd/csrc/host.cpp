@@ -354,15 +354,20 @@ int do_deposit(Ctx& c, const float* pos) {
     c.density_is_delta = true;
     c.density_kept = !fused || c.keep_density;
   } else {
-    TIMED(c, ST_ZERO, launch_fill_zero(c.rho, cells * 8, c.stream));
+    // the first pass leaves the mesh cleared; one that may not be (never used, or a failure in
+    // between) is cleared here
+    if (!c.rho_clean) TIMED(c, ST_ZERO, launch_fill_zero(c.rho, cells * 8, c.stream));
+    const bool was_clean = c.rho_clean;
+    c.rho_clean = false;
     TIMED(c, ST_DEPOSIT, launch_deposit(pos, c.rho, c.Np, c.nbox, c.N, inv_cell, c.d_flags,
                                         c.tune.deposit_mode, c.tune.deposit_block, c.stream));
     if (zy)
       TIMED(c, ST_FWD_ZY, launch_fwd_zy(c.N, c.rho, nullptr, nullptr, nullptr, 0, c.ck[0], c.tw,
-                                        scale, c.nbox, c.stream));
+                                        scale, c.nbox, c.stream, c.delta));
     else
       TIMED(c, ST_FFT_Z, launch_fwd_z(c.N, c.rho, nullptr, nullptr, nullptr, 0, c.ck[1], c.tw,
-                                      scale, c.nbox, c.stream, c.tune.fft[0]));
+                                      scale, c.nbox, c.stream, c.tune.fft[0], c.delta));
+    c.rho_clean = !c.capturing || was_clean;     // what is captured has not run
     c.density_is_delta = false;
     c.density_kept = true;
   }
@@ -1067,7 +1072,8 @@ int pm_nu_copy_density(pm_nu_ctx* ctx, int box, float* out) {
           ? launch_delta_to_density(c->delta + box * c->M, out, c->M,
                                     static_cast<float>(static_cast<double>(c->Np) / c->M),
                                     c->stream)
-          : launch_fixed_to_float(c->rho + box * c->M, out, c->M, c->stream);
+          : hipMemcpyAsync(out, c->delta + box * c->M, c->M * sizeof(float),
+                           hipMemcpyDeviceToDevice, c->stream);
   if (e != hipSuccess) return set_error(PM_NU_EHIP, "copy_density: %s", hipGetErrorString(e));
   return PM_NU_OK;
 }
@@ -1211,6 +1217,10 @@ int pm_nu_graph_launch(pm_nu_ctx* ctx) {
   if (!c->graph_exec)
     return set_error(PM_NU_ESTATE,
                      "no captured graph (none captured, or a setting changed since capture)");
+  if (!c->rho_clean && c->tune.deposit_mode < 6) {   // a failed deposit since the capture
+    PMNU_HIP(launch_fill_zero(c->rho, c->M * c->nbox * 8, c->stream));
+    c->rho_clean = true;
+  }
   PMNU_HIP(hipGraphLaunch(c->graph_exec, c->stream));
   return PM_NU_OK;
 }

@@ -175,7 +175,8 @@ struct Ctx {
   int* n_fb = nullptr;             // [2] chunks that used the side grid this deposit; running
                                    // total of earlier deposits (added by the first FFT pass)
   unsigned fb_seen = 0;            // running total at the last pm_nu_side_grid_uses
-  float* delta = nullptr;          // [nbox][M] delta in FP32 (modes 6, 7)
+  float* delta = nullptr;          // [nbox][M] delta in FP32 (modes 6, 7), or the density
+  bool rho_clean = false;          // rho is zero (once the launched work has run)
   double* d_kd = nullptr;          // [nbox][2] kick and drift factors of the leapfrog
   // pinned staging of the host-built arrays (copied in stream order) and the last copies
   double* h_tg = nullptr;          // ds [nbox][qcap], then w, then log2 ds
@@ -258,8 +259,6 @@ constexpr int kPatchFewChunks = 256, kPatchFewTile = 18432;
 // would add one by one
 constexpr int kSideBoxMax = 8 * kPatchCH;
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);
-hipError_t launch_fixed_to_float(const unsigned long long* src, float* dst, int64_t n,
-                                 hipStream_t s);
 hipError_t launch_extract_component(const float* src, float* dst, int64_t n, int comp,
                                    hipStream_t s);
 // mode 0: one thread per particle, 8 global atomics each; modes 1-3: LDS-privatised
@@ -277,19 +276,20 @@ hipError_t launch_interp(const float* pos, const float* force, float* acc, int64
 // input: the fixed-point density rho, or (if delta is not NULL) delta in FP32; reset[0] (may
 // be NULL) is added to reset[1] and cleared by the kernel when reading delta, and the n_clear
 // ints at clear are cleared
-// (NULL: none); a clear larger than the launch's thread count is rejected
-hipError_t launch_fwd_z(int N, const unsigned long long* rho, const float* delta, int* reset,
+// (NULL: none); a clear larger than the launch's thread count is rejected. rho_out (may be NULL,
+// not with delta): receives the density in FP32, and rho is cleared
+hipError_t launch_fwd_z(int N, unsigned long long* rho, float* delta, int* reset,
                         int* clear, int n_clear, float2* out, const float2* tw, double scale,
-                        int nbox, hipStream_t s, int v = 0);
+                        int nbox, hipStream_t s, int v = 0, float* rho_out = nullptr);
 // reset, clear, n_clear: the patch registry's end-of-step work after launch_patch_fwd_z
 hipError_t launch_fwd_y(int N, const float2* in, float2* out, const float2* tw, int nbox,
                         hipStream_t s, int v = 0, int* reset = nullptr, int* clear = nullptr,
                         int n_clear = 0);
 // N <= 128: fwd_z and fwd_y in one kernel (rho or delta in as for launch_fwd_z; out: the
 // y-transformed modes fwd_y would write)
-hipError_t launch_fwd_zy(int N, const unsigned long long* rho, const float* delta, int* reset,
+hipError_t launch_fwd_zy(int N, unsigned long long* rho, float* delta, int* reset,
                          int* clear, int n_clear, float2* out, const float2* tw, double scale,
-                         int nbox, hipStream_t s);
+                         int nbox, hipStream_t s, float* rho_out = nullptr);
 // the patch sums and the first (z) forward pass in one kernel (N >= 32); delta_out, when
 // given, also receives delta
 hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const int* reg_count,
