@@ -119,8 +119,8 @@ def kernel_name(stage, tuning, n_mesh):
     if stage == "patch_fwd_z":
         return "patch_fwd_z_kernel<%d>" % n_mesh
     if stage == "fft_fwd_zy":
-        return "fwd_zy_kernel<%d, %s>" % (n_mesh, "true" if tuning["deposit_mode"] >= 6
-                                          else "false")
+        return "fwd_zy_kernel<%d, %s" % (n_mesh, "true" if tuning["deposit_mode"] >= 6
+                                         else "false")   # , threads by the number of planes>
     if stage == "fft_fwd_z":
         return "fwd_z_kernel<%d, %s, %d>" % (n_mesh, "true" if tuning["deposit_mode"] >= 6
                                              else "false", tiles.get("fwd_z", 0))

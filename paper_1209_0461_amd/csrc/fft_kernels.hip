@@ -560,14 +560,12 @@ __global__ __launch_bounds__(NT) void fwd_y_kernel(const float2* __restrict__ in
 // transformed as in fwd_y_kernel and written to [box][k_z][x][k_y]. The same arithmetic in the
 // same order as the two passes, so the same modes bit for bit; the z-transformed plane never
 // reaches HBM. With DELTA it also does fwd_z_kernel's registry work (reset, clear).
-constexpr int kFwdZYNT = 256;   // threads per workgroup of fwd_zy_kernel
-template <int N, bool DELTA>
-__global__ __launch_bounds__(kFwdZYNT) void fwd_zy_kernel(void* in, float2* __restrict__ out,
+template <int N, bool DELTA, int NT>
+__global__ __launch_bounds__(NT) void fwd_zy_kernel(void* in, float2* __restrict__ out,
                                                           const float2* __restrict__ twg,
                                                           double scale, int* __restrict__ reset,
                                                           int* __restrict__ clear, int n_clear,
                                                           float* __restrict__ rho_out) {
-  constexpr int NT = kFwdZYNT;                     // this kernel's workgroup size
   constexpr int NL = N / 2, ES = NL + 1, NK = Shape<N>::NK, ES2 = NK + 1;
   constexpr int LDS_N = N * (ES > ES2 ? ES : ES2);
   constexpr int PER = (NK * N + NT - 1) / NT;      // half-spectrum values per thread
@@ -1426,16 +1424,26 @@ template <int N> struct FwdZY {
     if constexpr (N > 128) {
       return hipErrorInvalidValue;                 // the plane does not fit the LDS
     } else {
-      dim3 grid(N, nbox);
-      if (static_cast<int64_t>(grid.x) * grid.y * kFwdZYNT < n_clear)
-        return hipErrorInvalidValue;               // every count needs a thread to clear it
-      if (delta)
-        hipLaunchKernelGGL((fwd_zy_kernel<N, true>), grid, dim3(kFwdZYNT), 0, s, delta, out, tw,
-                           scale, reset, clear, n_clear, nullptr);
-      else
-        hipLaunchKernelGGL((fwd_zy_kernel<N, false>), grid, dim3(kFwdZYNT), 0, s, rho, out, tw,
-                           scale, reset, clear, n_clear, rho_out);
-      return hipGetLastError();
+      // Threads a plane: with few planes each CU has one, and more waves on it hide more of its
+      // latencies. us with 256 / 512 / 1024 threads: one 128^3 box 17.6 / 14.5 / 13.6, four
+      // 27.3 / 24.5 / 24.5, sixteen 82 / 73; one 64^3 box 9.2 / 8.0 / 7.9, eight 11.0 / 10.3 /
+      // 10.2, sixteen 15.0 / 15.1, sixty-four 35.1 / 36.2 / 43.4.
+      const int64_t planes = static_cast<int64_t>(N) * nbox;
+      const auto go = [&](auto nt) -> hipError_t {
+        constexpr int NT = decltype(nt)::value;
+        const dim3 grid(N, nbox);
+        if (planes * NT < n_clear) return hipErrorInvalidValue;   // every count needs a thread
+        if (delta)
+          hipLaunchKernelGGL((fwd_zy_kernel<N, true, NT>), grid, dim3(NT), 0, s, delta, out, tw,
+                             scale, reset, clear, n_clear, nullptr);
+        else
+          hipLaunchKernelGGL((fwd_zy_kernel<N, false, NT>), grid, dim3(NT), 0, s, rho, out, tw,
+                             scale, reset, clear, n_clear, rho_out);
+        return hipGetLastError();
+      };
+      constexpr int FEW = N == 128 ? 1024 : N == 64 ? 512 : 256, MANY = N == 128 ? 512 : 256;
+      return planes <= (N == 128 ? 256 : 1024) ? go(std::integral_constant<int, FEW>{})
+                                               : go(std::integral_constant<int, MANY>{});
     }
   }
 };
