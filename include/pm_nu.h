@@ -258,7 +258,8 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
  * 0 (direct gather; interp_block = particles per workgroup, rounded down to 256, 512 or
  * 1024) or 1/2/3 (LDS-staged chunks). Blocks: multiples of 64 in 64..1024. Until this or
  * pm_nu_autotune is called: deposit_mode 6 for N >= 64 (4 below, where one coarse cell
- * covers the mesh, and for few particles on small meshes), interp_mode 1. */
+ * covers the mesh, and for few particles on small meshes), interp_mode 1 (0 up to 2^21
+ * particles, or one for two nodes). */
 int pm_nu_set_launch(pm_nu_ctx* ctx, int deposit_mode, int deposit_block, int interp_mode,
                      int interp_block);
 /* Tile candidates of the six FFT passes, candidates[6] (host) in the order fwd_z (real rows

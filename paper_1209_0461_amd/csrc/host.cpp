@@ -319,6 +319,19 @@ int default_deposit_mode(int n, int nbox, int64_t np) {
   return few ? 4 : 6;
 }
 
+// Particles gather straight from the force grid (mode 0) instead of from boxes of it staged in LDS
+// (mode 1) where
+//   - there are at most half as many as nodes, each then reads more of a staged box than it uses
+//     (256 a workgroup; us, staged / direct: 256^3 mesh with 154^3 particles 100 / 77, 180^3
+//     123 / 93, 200^3 146 / 114, in C order 110 / 101; 512^3 with 256^3 519 / 468, 360^3 813 /
+//     656; 64 boxes of 64^3 with 38^3 111 / 78; nearer one a node it turns: 512^3 with 440^3
+//     881 / 940, 256^3 with 240^3 123 / 159, with 256^3 138 / 184);
+//   - there are at most 2^21, whose force grid the caches hold while few workgroups cannot hide
+//     the three memory latencies of a staged box (512 a workgroup: 32^3 10.5 / 6.4, 64^3 10.6 /
+//     7.0, four 64^3 boxes 16.2 / 13.4, eight 22.7 / 21.7, 128^3 22.0 / 22.1, displaced by 1.5
+//     cells 24.7 / 22.9, in C order 22.6 / 15.8; 128 boxes of 32^3 35.6 / 38.0).
+constexpr int64_t kDirectInterp = int64_t{1} << 21;
+
 int do_deposit(Ctx& c, const float* pos) {
   if (!pos) return set_error(PM_NU_EINVAL, "pos is NULL");
   const int64_t cells = c.M * c.nbox;
@@ -560,6 +573,8 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   for (int v = 1; v < 3; ++v) max_partial = std::max(max_partial, fwd_x_partials(c->N, v));
   c->n_partial_cap = max_partial;
   c->tune.deposit_mode = default_deposit_mode(c->N, c->nbox, c->Np);
+  c->tune.interp_mode = 2 * c->Np <= c->M || c->Np * c->nbox <= kDirectInterp ? 0 : 1;
+  c->tune.interp_block = 2 * c->Np <= c->M ? 256 : 512;
   c->stream = static_cast<hipStream_t>(cfg->stream);
   c->m_nu.assign(m_nu_total, m_nu_total + c->nbox);
   for (int b = 0; b < c->nbox; ++b) {
