@@ -497,13 +497,10 @@ void free_ctx(Ctx* c) {
                   c->ratio, c->hist_pm, c->hist_pnu, c->ic_pnu, c->ic_theta, c->tg_ds,
                   c->tg_l2, c->tg_w, c->d_resp, c->ridx, c->d_next, c->tw, c->inv_w2,
                   c->d_flags, c->patches, c->reg_count, c->reg_list, c->rho_fb, c->n_fb,
-                  c->delta, c->d_kd, c->d_up};
+                  c->delta, c->d_kd};
   for (void* p : bufs)
     if (p) hipFree(p);
-  for (void* p : {static_cast<void*>(c->h_tg), static_cast<void*>(c->h_resp),
-                  static_cast<void*>(c->h_kd), static_cast<void*>(c->h_spec),
-                  static_cast<void*>(c->h_up)})
-    if (p) hipHostFree(p);
+  if (c->h_tg) hipHostFree(c->h_tg);
   delete c;
 }
 
@@ -635,22 +632,26 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
     ALLOC(c->reg_count, coarse);
     ALLOC(c->reg_list, coarse * 32);
     ALLOC(c->rho_fb, nb * c->M);
-    ALLOC(c->n_fb, 2);
+    ALLOC(c->n_fb, 3);
+    c->d_up = c->n_fb + 2;
     ALLOC(c->delta, nb * c->M);
   }
   ALLOC(c->d_kd, 2 * nb);
-  ALLOC(c->d_up, 1);
 #undef ALLOC
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_tg), 3 * nb * c->qcap * sizeof(double)) !=
-          hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->h_resp), nb * sizeof(RespBox)) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->h_kd), 2 * nb * sizeof(double)) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->h_spec), (3 * B + 1) * sizeof(double)) !=
-          hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->h_up), sizeof(uint32_t)) != hipSuccess) {
+  // the pinned staging in one allocation (each costs about 0.1 ms)
+  const size_t n_tg = 3 * nb * c->qcap * sizeof(double), n_resp = nb * sizeof(RespBox),
+               n_kd = 2 * nb * sizeof(double), n_spec = (3 * B + 1) * sizeof(double);
+  char* pinned = nullptr;
+  if (hipHostMalloc(reinterpret_cast<void**>(&pinned),
+                    n_tg + n_resp + n_kd + n_spec + sizeof(uint32_t)) != hipSuccess) {
     free_ctx(c);
     return set_error(PM_NU_ENOMEM, "pinned staging could not be allocated");
   }
+  c->h_tg = reinterpret_cast<double*>(pinned);
+  c->h_resp = reinterpret_cast<RespBox*>(pinned + n_tg);
+  c->h_kd = reinterpret_cast<double*>(pinned + n_tg + n_resp);
+  c->h_spec = reinterpret_cast<double*>(pinned + n_tg + n_resp + n_kd);
+  c->h_up = reinterpret_cast<uint32_t*>(pinned + n_tg + n_resp + n_kd + n_spec);
   std::memset(c->h_tg, 0, 3 * nb * c->qcap * sizeof(double));
   *c->h_up = 0;
   c->tgc.resize(c->nbox);
@@ -697,8 +698,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   // the patch deposit keeps these at zero between deposits
   e = e ? e : hipMemset(c->reg_count, 0, nb * patch_coarse_cells(c->N) * sizeof(int));
   e = e ? e : hipMemset(c->rho_fb, 0, nb * c->M * sizeof(unsigned long long));
-  e = e ? e : hipMemset(c->n_fb, 0, 2 * sizeof(int));
-  e = e ? e : hipMemset(c->d_up, 0, sizeof(int));
+  e = e ? e : hipMemset(c->n_fb, 0, 3 * sizeof(int));   // and d_up
   e = e ? e : hipDeviceSynchronize();
   if (e != hipSuccess) {
     free_ctx(c);

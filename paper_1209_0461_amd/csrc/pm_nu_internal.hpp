@@ -179,6 +179,7 @@ struct Ctx {
   bool rho_clean = false;          // rho is zero (once the launched work has run)
   double* d_kd = nullptr;          // [nbox][2] kick and drift factors of the leapfrog
   // pinned staging of the host-built arrays (copied in stream order) and the last copies
+  // (one allocation, from h_tg on)
   double* h_tg = nullptr;          // ds [nbox][qcap], then w, then log2 ds
   RespBox* h_resp = nullptr;       // [nbox]
   double* h_kd = nullptr;          // [nbox][2]
@@ -190,7 +191,7 @@ struct Ctx {
   // the upload itself) and its count of finished workgroups
   uint32_t up_seq = 0;
   uint32_t* h_up = nullptr;
-  int* d_up = nullptr;
+  int* d_up = nullptr;             // n_fb[2]
   bool kd_staged = false;          // h_kd goes up with the next time grid
   bool density_is_delta = false;   // the last deposit wrote delta (modes 6..9), not rho
   bool keep_density = false;       // modes 8, 9: also store delta (pm_nu_set_keep_density)
