@@ -32,7 +32,10 @@ namespace {
 // for an FP32 coordinate times an FP64 inverse cell size up to the product's rounding).
 // The node index comes from adding 1.5 * 2^52, which leaves floor(u) in two's complement
 // in the low bits for |u| < 2^51; the mask keeps any index in range.
+// The product is rounded by itself in every deposit (no fused multiply-subtract for the fraction,
+// which the compiler would form in some of them), so that all give the same fixed-point weights.
 __device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int& i, double& d) {
+#pragma clang fp contract(off)
   const double u = static_cast<double>(x) * inv_cell;
   const double f = floor(u);
   d = u - f;
@@ -299,6 +302,7 @@ __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt
 constexpr double kFloorMagic = 6755399441055744.0;     // 1.5 * 2^52
 __device__ __forceinline__ void box_axis(float x, double inv_cell, double mg, int nmask, int& t,
                                          double& d) {
+#pragma clang fp contract(off)               // as axis64
   const double u = static_cast<double>(x) * inv_cell;
   const double f = floor(u);
   d = u - f;
