@@ -248,8 +248,8 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
 /* Set the launch shapes directly: deposit_mode 0 (one thread per particle, global atomics;
  * deposit_block = threads per workgroup), 1..5 (LDS-privatised chunks of 1024/2048/4096
  * particles on 256 threads, 4096 on 512 threads, 8192 on 1024 threads, flushed with global
- * atomics; mode 4 takes 512 on 256 threads for N <= 32 and for few particles), 6 (chunks of 4096 written to per-chunk patches and summed per 16^3 coarse
- * cell without atomics; a box beyond the LDS tile's 6144 nodes takes several
+ * atomics; mode 4 takes 512 on 256 threads for N <= 32 and for few particles), 6 (chunks of 4096, or 2048 or 1024 where
+ * particles are sparse, written to per-chunk patches and summed per 16^3 coarse cell without atomics; a box beyond the LDS tile's 6144 nodes takes several
  * passes; a chunk whose box exceeds 26624 nodes, or its part in a coarse cell already listing
  * 32 patches, goes through atomics on a side grid),
  * 7 (as 6 with a tile of 9216 nodes, at lower occupancy), 8 and 9 (as 6 and 7 with

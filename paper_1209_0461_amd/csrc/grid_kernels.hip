@@ -1158,20 +1158,40 @@ int64_t patch_coarse_cells(int n) {
   const int64_t nc = n >> patch_cb_log2(n);
   return nc * nc * nc;
 }
-int64_t patch_chunks(int64_t np) { return (np + kPatchCH - 1) / kPatchCH; }
+// Particles a chunk of the patch deposit: a chunk of 4096 of sparse particles spans a box beyond
+// the patch slot's 26624 nodes as soon as it straddles two blocks of the curve, and goes through
+// atomics. A step, us, with 4096 / 2048 / 1024: 256^3 mesh with 128^3 particles 644 / 425 / 421,
+// 154^3 645 / 565 / 559, 180^3 693 / 575 / 554, 200^3 503 / 498 / 516, 220^3 748 / 651 / 656; 512^3
+// with 310^3 5126 / 4468 / 4193; 64 boxes of 64^3 with 40^3 587 / 392 / 375. Nearer a particle a
+// node smaller chunks lose (more halo): 256^3 with 240^3 517 / 530, 256^3 526 / 540. So 1024 up
+// to 3/8 of a particle a node, 2048 up to 3/4.
+int patch_chunk_particles(int64_t np, int n) {
+  const int64_t m = static_cast<int64_t>(n) * n * n;
+  return 8 * np <= 3 * m ? 1024 : 4 * np <= 3 * m ? 2048 : kPatchCH;
+}
+int64_t patch_chunks(int64_t np, int n) {
+  const int ch = patch_chunk_particles(np, n);
+  return (np + ch - 1) / ch;
+}
 
 hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, int* reg_count,
                                 int4* reg_list, unsigned long long* rho_fb, int* n_fb,
                                 int64_t np, int nbox, int n, double inv_cell, int* flags,
                                 bool big_tile, hipStream_t s) {
   if (n > 1024) return hipErrorInvalidValue;     // registry entries pack indices in 10 bits
-  const int64_t chunks = patch_chunks(np);
+  const int64_t chunks = patch_chunks(np, n);
   const dim3 grid(static_cast<unsigned>(chunks * nbox));
+  const int ch = patch_chunk_particles(np, n);
   const auto launch = [&](auto tile) {
     constexpr int TILE = decltype(tile)::value;
-    hipLaunchKernelGGL((deposit_patch_kernel<kPatchCH, TILE, kPatchNT>), grid, dim3(kPatchNT), 0, s,
-                       pos, patches, reg_count, reg_list, rho_fb, n_fb, np, n, inv_cell, flags,
-                       chunks, patch_cb_log2(n));
+    const auto go = [&](auto part) {
+      hipLaunchKernelGGL((deposit_patch_kernel<decltype(part)::value, TILE, kPatchNT>), grid,
+                         dim3(kPatchNT), 0, s, pos, patches, reg_count, reg_list, rho_fb, n_fb, np,
+                         n, inv_cell, flags, chunks, patch_cb_log2(n));
+    };
+    if (ch == kPatchCH) go(std::integral_constant<int, kPatchCH>{});
+    else if (ch == 2048) go(std::integral_constant<int, 2048>{});
+    else go(std::integral_constant<int, 1024>{});
   };
   // one 64^3 box (64 chunks): 13.2 -> 13.4 us for boxes of one pass, 20.8 -> 18.8 (displaced by
   // two cells) and 24.2 -> 19.2 (C order) for those that the smaller tile takes several for

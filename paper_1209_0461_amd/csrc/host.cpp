@@ -313,7 +313,7 @@ namespace {
 // one coarse cell would cover the mesh (N < 64).
 int default_deposit_mode(int n, int nbox, int64_t np) {
   if (n < 64) return 4;
-  const int64_t nodes = static_cast<int64_t>(n) * n * n * nbox, chunks = patch_chunks(np) * nbox;
+  const int64_t nodes = static_cast<int64_t>(n) * n * n * nbox, chunks = (np + 4095) / 4096 * nbox;
   const bool few = (chunks <= 64 && nodes <= 128 * 128 * 128) ||
                    (chunks <= 256 && nodes <= 2 * 64 * 64 * 64);
   return few ? 4 : 6;
@@ -626,7 +626,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   ALLOC(c->inv_w2, static_cast<size_t>(c->N));
   ALLOC(c->d_flags, 1);
   {
-    const size_t chunks = nb * static_cast<size_t>(patch_chunks(c->Np));
+    const size_t chunks = nb * static_cast<size_t>(patch_chunks(c->Np, c->N));
     const size_t coarse = nb * static_cast<size_t>(patch_coarse_cells(c->N));
     ALLOC(c->patches, chunks * kPatchSlot);
     ALLOC(c->reg_count, coarse);

@@ -371,7 +371,9 @@ hipError_t launch_surrogate_dataset(const RespBox* boxes, const double* pcdm, co
                                     float* x, float* y, hipStream_t s);
 int patch_cb_log2(int n);
 int64_t patch_coarse_cells(int n);
-int64_t patch_chunks(int64_t np);
+// particles a chunk of the patch deposit, and its chunks
+int patch_chunk_particles(int64_t np, int n);
+int64_t patch_chunks(int64_t np, int n);
 // big_tile: the kPatchCap-node LDS tile (mode 7) instead of kPatchTile (mode 6); reg_list
 // entries are (chunk, packed box origin, packed extents, 0), n <= 1024
 hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, int* reg_count,
