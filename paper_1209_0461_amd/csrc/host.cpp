@@ -302,19 +302,19 @@ int prepare_time_grid(Ctx& c, double a_now) {
 
 namespace {
 
-// The patch deposit (mode 6) gives each 4096-particle chunk a workgroup and each coarse cell a
-// sum over its patches; with few chunks that leaves the chip idle twice, and clearing the mesh
-// and adding chunks of 512 particles to it by atomics (mode 4) is faster. A step in modes 6 and
-// 4, us, displacements of 0.3 / 2 cells: 64^3 mesh with 24^3 particles 76 / 100 and 52 / 58, 64^3
-// 60 / 67 and 53 / 58, 100^3 108 / 122 and 65 / 71; two boxes of 64^3 67 / 73 and 63 / 70, four
-// of 40^3 particles 90 / 117 and 65 / 114, of 64^3 76 / 88 and 77 / 86; a 128^3 mesh with 64^3
-// particles 135 / 170 and 130 / 157, 80^3 104 / 120 and 108 / 208. So mode 4 up to 64 chunks on
-// meshes up to 128^3 nodes, and up to 256 on meshes up to two boxes of 64^3; and always where
-// one coarse cell would cover the mesh (N < 64).
+// The patch deposit (mode 6) gives each chunk a workgroup and each coarse cell a sum over its
+// patches; with few particles that leaves the chip idle twice, and adding chunks of 512 particles
+// to a cleared mesh by atomics (mode 4) is faster. A step in modes 6 and 4, us: 64^3 mesh with
+// 40^3 particles 45 / 38, 64^3 60 / 53, 100^3 108 / 65; two boxes of 64^3 67 / 63, four of 40^3
+// particles 62 / 57, of 64^3 76 / 77; a 128^3 mesh with 40^3 particles 91 / 82, 64^3 84 / 110.
+// So mode 4 (counted in chunks of 4096) up to 16 chunks on meshes up to 128^3 nodes, up to 64 on
+// four boxes of 64^3, up to 256 on two; and always where one coarse cell would cover the mesh
+// (N < 64).
 int default_deposit_mode(int n, int nbox, int64_t np) {
   if (n < 64) return 4;
   const int64_t nodes = static_cast<int64_t>(n) * n * n * nbox, chunks = (np + 4095) / 4096 * nbox;
-  const bool few = (chunks <= 64 && nodes <= 128 * 128 * 128) ||
+  const bool few = (chunks <= 16 && nodes <= 128 * 128 * 128) ||
+                   (chunks <= 64 && nodes <= 4 * 64 * 64 * 64) ||
                    (chunks <= 256 && nodes <= 2 * 64 * 64 * 64);
   return few ? 4 : 6;
 }

@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n_mesh,n_boxes,n_part,default", [
     (32, 1, 40000, 4), (64, 1, 256 * 4096, 4), (64, 1, 256 * 4096 + 1, 6), (64, 2, 128 * 4096, 4),
-    (64, 3, 21 * 4096, 4), (64, 3, 22 * 4096, 6), (64, 9, 4096, 6), (128, 1, 64 * 4096, 4),
-    (128, 1, 64 * 4096 + 1, 6), (128, 2, 4096, 6), (256, 1, 4096, 6)])
+    (64, 3, 21 * 4096, 4), (64, 3, 22 * 4096, 6), (64, 9, 4096, 6), (128, 1, 16 * 4096, 4),
+    (128, 1, 16 * 4096 + 1, 6), (128, 2, 4096, 6), (256, 1, 4096, 6)])
 def test_default_deposit(n_mesh, n_boxes, n_part, default):
     import torch
     from paper_1209_0461_amd import PMNu, binding
