@@ -31,15 +31,19 @@ namespace {
 // Per axis: lower node (mod N) and the fraction beyond it, in FP64 (u = x N / L is exact
 // for an FP32 coordinate times an FP64 inverse cell size up to the product's rounding).
 // The node index comes from adding 1.5 * 2^52, which leaves floor(u) in two's complement
-// in the low bits for |u| < 2^51; the mask keeps any index in range.
+// in the low bits for |u| < 2^51; the mask keeps any index in range. (Beyond, the coordinate's own
+// spacing is more than a box; every deposit and interpolation takes the place found here.)
 // The product is rounded by itself in every deposit (no fused multiply-subtract for the fraction,
 // which the compiler would form in some of them), so that all give the same fixed-point weights.
-__device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int& i, double& d) {
+__device__ __forceinline__ unsigned axis_bits(float x, double inv_cell, double& d) {
 #pragma clang fp contract(off)
   const double u = static_cast<double>(x) * inv_cell;
   const double f = floor(u);
   d = u - f;
-  i = static_cast<int>(__double2loint(f + 6755399441055744.0)) & nmask;
+  return static_cast<unsigned>(__double2loint(f + 6755399441055744.0));
+}
+__device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int& i, double& d) {
+  i = static_cast<int>(axis_bits(x, inv_cell, d)) & nmask;
 }
 
 // The product a b, 0 <= a b < 2^52, rounded to the nearest integer (ties to even): adding 2^52
@@ -297,16 +301,12 @@ __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt
   }
 }
 
-// A particle's lower node relative to the box origin and its fraction on one axis; mg is
-// kFloorMagic - g0, so that the node comes out relative to g0 in one addition.
-constexpr double kFloorMagic = 6755399441055744.0;     // 1.5 * 2^52
-__device__ __forceinline__ void box_axis(float x, double inv_cell, double mg, int nmask, int& t,
+// A particle's lower node relative to the box origin g0 and its fraction on one axis. g0 comes off
+// in integers: taken off the magic number instead, as one addition, it agrees with axis64 only
+// for |u| < 2^51, and the place of a finite coordinate beyond lay outside the box.
+__device__ __forceinline__ void box_axis(float x, double inv_cell, int g0, int nmask, int& t,
                                          double& d) {
-#pragma clang fp contract(off)               // as axis64
-  const double u = static_cast<double>(x) * inv_cell;
-  const double f = floor(u);
-  d = u - f;
-  t = static_cast<int>(__double2loint(f + mg)) & nmask;
+  t = static_cast<int>(axis_bits(x, inv_cell, d) - static_cast<unsigned>(g0)) & nmask;
 }
 
 // Strides of an ey x ez plane in an LDS tile: padded so that a wave's 16-lane groups of
@@ -341,21 +341,20 @@ __device__ __forceinline__ void add_chunk(const Chunk<PPT>& c, unsigned long lon
                                           double inv_cell, int nmask, int sy, int sz, int p0,
                                           int npl) {
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2], plane = sy * sz;
-  const double mx = kFloorMagic - c.g0[0], my = kFloorMagic - c.g0[1], mz = kFloorMagic - c.g0[2];
 #pragma unroll
   for (int q = 0; q < PPT; ++q) {
     if (!((c.ok >> q) & 1u)) continue;
     int t[3];
     double d[3];
-    box_axis(c.p[q][0], inv_cell, mx, nmask, t[0], d[0]);
+    box_axis(c.p[q][0], inv_cell, c.g0[0], nmask, t[0], d[0]);
     if constexpr (!WHOLE) {
       const int up = t[0] + 1 < ex ? t[0] + 1 : 0;
       if (static_cast<unsigned>(t[0] - p0) >= static_cast<unsigned>(npl) &&
           static_cast<unsigned>(up - p0) >= static_cast<unsigned>(npl))
         continue;
     }
-    box_axis(c.p[q][1], inv_cell, my, nmask, t[1], d[1]);
-    box_axis(c.p[q][2], inv_cell, mz, nmask, t[2], d[2]);
+    box_axis(c.p[q][1], inv_cell, c.g0[1], nmask, t[1], d[1]);
+    box_axis(c.p[q][2], inv_cell, c.g0[2], nmask, t[2], d[2]);
     const double wx[2] = {(1.0 - d[0]) * kFixScale, d[0] * kFixScale};
     const double wy[2] = {1.0 - d[1], d[1]};
     const double wz[2] = {1.0 - d[2], d[2]};
@@ -987,7 +986,7 @@ __global__ __launch_bounds__(256, CH <= 1024 ? 6 : 1) void interp_tiled_kernel(c
     for (int a = 0; a < 3; ++a) {
       int t;
       double d;
-      box_axis(c.p[q][a], inv_cell, kFloorMagic - c.g0[a], nmask, t, d);
+      box_axis(c.p[q][a], inv_cell, c.g0[a], nmask, t, d);
       rel[q] |= t << (10 * a);
       fr[q][a] = static_cast<float>(d);
     }
