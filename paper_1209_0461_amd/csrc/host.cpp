@@ -332,6 +332,13 @@ int default_deposit_mode(int n, int nbox, int64_t np) {
 //     cells 24.7 / 22.9, in C order 22.6 / 15.8; 128 boxes of 32^3 35.6 / 38.0).
 constexpr int64_t kDirectInterp = int64_t{1} << 21;
 
+// The stream is being captured, by pm_nu_graph_capture or by the caller.
+bool in_capture(const Ctx& c) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+  return c.capturing || hipStreamIsCapturing(c.stream, &status) != hipSuccess ||
+         status != hipStreamCaptureStatusNone;
+}
+
 int do_deposit(Ctx& c, const float* pos) {
   if (!pos) return set_error(PM_NU_EINVAL, "pos is NULL");
   const int64_t cells = c.M * c.nbox;
@@ -367,8 +374,8 @@ int do_deposit(Ctx& c, const float* pos) {
     c.density_is_delta = true;
     c.density_kept = !fused || c.keep_density;
   } else {
-    // the first pass leaves the mesh cleared; one that may not be (never used, or a failure in
-    // between) is cleared here
+    // the mesh is cleared at init and left cleared by the first pass; one that may not be (a
+    // failure in between) is cleared here
     if (!c.rho_clean) TIMED(c, ST_ZERO, launch_fill_zero(c.rho, cells * 8, c.stream));
     const bool was_clean = c.rho_clean;
     c.rho_clean = false;
@@ -380,7 +387,7 @@ int do_deposit(Ctx& c, const float* pos) {
     else
       TIMED(c, ST_FFT_Z, launch_fwd_z(c.N, c.rho, nullptr, nullptr, nullptr, 0, c.ck[1], c.tw,
                                       scale, c.nbox, c.stream, c.tune.fft[0], c.delta));
-    c.rho_clean = !c.capturing || was_clean;     // what is captured has not run
+    c.rho_clean = was_clean || !in_capture(c);   // what is captured has not run
     c.density_is_delta = false;
     c.density_kept = true;
   }
@@ -695,7 +702,8 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   e = e ? e : hipMemset(c->pcdm, 0, nb * B * sizeof(double));
   e = e ? e : hipMemset(c->pnu, 0, nb * B * sizeof(double));
   e = e ? e : hipMemset(c->ratio, 0, nb * B * sizeof(double));
-  // the patch deposit keeps these at zero between deposits
+  // the deposits keep these at zero between them
+  e = e ? e : hipMemset(c->rho, 0, nb * c->M * sizeof(unsigned long long));
   e = e ? e : hipMemset(c->reg_count, 0, nb * patch_coarse_cells(c->N) * sizeof(int));
   e = e ? e : hipMemset(c->rho_fb, 0, nb * c->M * sizeof(unsigned long long));
   e = e ? e : hipMemset(c->n_fb, 0, 3 * sizeof(int));   // and d_up
@@ -704,6 +712,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
     free_ctx(c);
     return set_error(PM_NU_EHIP, "init upload failed: %s", hipGetErrorString(e));
   }
+  c->rho_clean = true;
   c->hist_a.assign(c->nbox, {});
   c->has_ic.assign(c->nbox, 0);
   c->n_cur.assign(c->nbox, -1);
