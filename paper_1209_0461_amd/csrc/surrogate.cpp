@@ -25,9 +25,8 @@ struct Surrogate {
   int64_t perm_cap = 0;
   double* chk_exact = nullptr; // [nbox][B]
   double* chk_sur = nullptr;   // [nbox][B]
-  unsigned short* packed = nullptr;  // bf16 image of W1..W3 for inference
+  unsigned short* packed = nullptr;  // bf16 image of W1..W3, always that of P
   double* sur_r = nullptr;     // [nbox][B] the network's R of the last response
-  bool packed_valid = false;   // cleared whenever the FP32 masters change
   bool loaded = false;
   int64_t step = 0;
 };
@@ -69,12 +68,16 @@ int ensure(Ctx& c) {
   return PM_NU_OK;
 }
 
-int reset_optimizer(Ctx& c) {
+// After new weights in P: the optimiser starts again, and the bfloat16 image is formed here (training
+// keeps it current by itself), so that no later call, which may be captured, has to.
+int new_weights(Ctx& c) {
   Surrogate* s = c.sur;
   PMNU_HIP(hipMemset(s->m, 0, kSurParams * sizeof(float)));
   PMNU_HIP(hipMemset(s->v, 0, kSurParams * sizeof(float)));
   s->step = 0;
-  s->packed_valid = false;
+  s->loaded = false;
+  PMNU_HIP(launch_pack_weights(s->P, s->packed, c.stream));
+  s->loaded = true;
   return PM_NU_OK;
 }
 
@@ -82,16 +85,6 @@ int need_loaded(Ctx* c) {
   if (!c) return set_error(PM_NU_EINVAL, "ctx is NULL");
   if (!c->sur || !c->sur->loaded)
     return set_error(PM_NU_ESURROGATE, "no surrogate weights (load or init first)");
-  return PM_NU_OK;
-}
-
-// the bfloat16 image of the current weights (training keeps it current by itself)
-int ensure_packed(Ctx& c) {
-  Surrogate* s = c.sur;
-  if (s->packed_valid) return PM_NU_OK;
-  hipError_t e = launch_pack_weights(s->P, s->packed, c.stream);
-  if (e != hipSuccess) return set_error(PM_NU_EHIP, "weight packing: %s", hipGetErrorString(e));
-  s->packed_valid = true;
   return PM_NU_OK;
 }
 
@@ -108,8 +101,6 @@ int surrogate_launch(Ctx& c, int mode, double norm) {
   int rc = need_loaded(&c);
   if (rc) return rc;
   Surrogate* s = c.sur;
-  rc = ensure_packed(c);
-  if (rc) return rc;
   timer_begin(c, ST_SURROGATE);
   hipError_t e = launch_surrogate_response(
       s->P, s->packed, mode, c.d_resp, c.bin_partial, c.n_partial, c.d_counts, c.d_kmean,
@@ -144,10 +135,7 @@ int pm_nu_surrogate_load(pm_nu_ctx* ctx, const float* blob, int64_t n_floats) {
   if (rc) return rc;
   PMNU_HIP(hipStreamSynchronize(c->stream));
   PMNU_HIP(hipMemcpy(c->sur->P, blob, kSurBlob * sizeof(float), hipMemcpyHostToDevice));
-  rc = reset_optimizer(*c);
-  if (rc) return rc;
-  c->sur->loaded = true;
-  return PM_NU_OK;
+  return new_weights(*c);
 }
 
 int pm_nu_surrogate_save(pm_nu_ctx* ctx, float* blob, int64_t n_floats) {
@@ -213,10 +201,7 @@ int pm_nu_surrogate_init(pm_nu_ctx* ctx, const float* x, const float* y, int64_t
   fill(kOffW3, 128, 128);
   fill(kOffW4, 128, 1);
   PMNU_HIP(hipMemcpy(c->sur->P, blob.data(), kSurBlob * sizeof(float), hipMemcpyHostToDevice));
-  rc = reset_optimizer(*c);
-  if (rc) return rc;
-  c->sur->loaded = true;
-  return PM_NU_OK;
+  return new_weights(*c);
 }
 
 int pm_nu_surrogate_train_part(pm_nu_ctx* ctx, const float* x, const float* y, int64_t n,
@@ -238,8 +223,6 @@ int pm_nu_surrogate_train_part(pm_nu_ctx* ctx, const float* x, const float* y, i
     PMNU_HIP(hipMalloc(&s->perm, n * sizeof(int)));
     s->perm_cap = n;
   }
-  rc = ensure_packed(*c);
-  if (rc) return rc;
   std::vector<int> perm(n);
   const int64_t nb = (n + batch - 1) / batch;
   const int64_t total = nb * total_epochs;
@@ -287,8 +270,6 @@ int pm_nu_surrogate_predict(pm_nu_ctx* ctx, const float* x, float* y, int64_t n)
   int rc = need_loaded(c);
   if (rc) return rc;
   if (!x || !y || n < 1) return set_error(PM_NU_EINVAL, "bad arguments");
-  rc = ensure_packed(*c);
-  if (rc) return rc;
   SUR_LAUNCH(launch_mlp_predict(c->sur->P, c->sur->packed, x, y, n, c->stream));
   return PM_NU_OK;
 }
@@ -300,8 +281,6 @@ int pm_nu_surrogate_grad(pm_nu_ctx* ctx, const float* x, const float* y, int64_t
   if (rc) return rc;
   if (!x || !y || !grad || n < 1) return set_error(PM_NU_EINVAL, "bad arguments");
   Surrogate* s = c->sur;
-  rc = ensure_packed(*c);
-  if (rc) return rc;
   int n_part = 0;
   SUR_LAUNCH(launch_mlp_train(s->P, s->packed, x, y, nullptr, 0, n, 1.0f / n, s->part, &n_part,
                               c->stream));

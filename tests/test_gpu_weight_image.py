@@ -1,0 +1,50 @@
+"""The bfloat16 image of the network's weights, which prediction, gradient and training read, is
+that of the current weights whatever comes first: a prediction that a caller captures."""
+import pytest
+
+from test_gpu_surrogate import _ctx, _data
+
+pytestmark = pytest.mark.gpu
+
+
+def _trained_blob():
+    import torch
+    from paper_1209_0461_amd import binding
+    ctx = _ctx()
+    x, y = (torch.from_numpy(v).cuda() for v in _data(512, 3))
+    binding.pm_nu_surrogate_init(ctx.h, x, y, 4)
+    blob = binding.pm_nu_surrogate_save(ctx.h)
+    ctx.close()
+    return blob
+
+
+def test_prediction_captured_before_any_other():
+    import torch
+    from paper_1209_0461_amd import PMNu, binding
+    blob = _trained_blob()
+    x = torch.from_numpy(_data(777, 9)[0]).cuda()
+    want = torch.zeros(777, device="cuda")
+    ctx = _ctx()
+    binding.pm_nu_surrogate_load(ctx.h, blob)
+    binding.pm_nu_surrogate_predict(ctx.h, x, want)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.isfinite(want).all() and want.std() > 0
+    stream = torch.cuda.Stream()
+    ctx = PMNu(8, 8, 32.0, 4, 8, [0.3], stream=stream.cuda_stream)
+    binding.pm_nu_surrogate_load(ctx.h, blob)
+    out, eager = torch.zeros(777, device="cuda"), torch.zeros(777, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        binding.pm_nu_surrogate_predict(ctx.h, x, out)
+    for _ in range(3):
+        eager.zero_()
+        out.zero_()
+        torch.cuda.synchronize()
+        binding.pm_nu_surrogate_predict(ctx.h, x, eager)
+        with torch.cuda.stream(stream):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(eager, want) and torch.equal(out, want)
+    ctx.close()
