@@ -48,3 +48,29 @@ def test_prediction_captured_before_any_other():
         torch.cuda.synchronize()
         assert torch.equal(eager, want) and torch.equal(out, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,batch", [(512, 64), (9000, 4096)])
+def test_image_follows_training(n, batch):
+    """After training the image has been kept current entry by entry; a context that loads the
+    trained weights forms it anew. Prediction reads W1, W2, W3, the gradient also the transposed
+    copies; both kernels sum in a fixed order, so equal images give equal bits."""
+    import torch
+    from paper_1209_0461_amd import binding
+    ctx, other = _ctx(), _ctx()
+    x, y = (torch.from_numpy(v).cuda() for v in _data(n, 3))
+    binding.pm_nu_surrogate_init(ctx.h, x, y, 4)
+    got = []
+    before = binding.pm_nu_surrogate_save(ctx.h)
+    binding.pm_nu_surrogate_train(ctx.h, x, y, 2, batch, 3e-3, 1)
+    blob = binding.pm_nu_surrogate_save(ctx.h)
+    assert (blob[:35329] != before[:35329]).mean() > 0.9
+    binding.pm_nu_surrogate_load(other.h, blob)
+    for c in (ctx, other):
+        out, g = torch.empty(n, device="cuda"), torch.empty(35329, device="cuda")
+        binding.pm_nu_surrogate_predict(c.h, x, out)
+        binding.pm_nu_surrogate_grad(c.h, x, y, g)
+        torch.cuda.synchronize()
+        got.append((out, g))
+        c.close()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
