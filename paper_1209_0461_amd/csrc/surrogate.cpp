@@ -17,7 +17,7 @@ namespace pmnu {
 
 struct Surrogate {
   float* P = nullptr;          // [kSurBlob] FP32 masters + statistics
-  float* part = nullptr;       // [mlp_part_floats()] gradient sums of the workgroups
+  float* part = nullptr;       // [mlp_part_floats()] gradient sums of the workgroups (ensure_part)
   float* m = nullptr;          // [kSurParams] Adam first moment
   float* v = nullptr;          // [kSurParams] Adam second moment
   float* loss = nullptr;       // [1]
@@ -50,7 +50,6 @@ int ensure(Ctx& c) {
   c.sur = s;
   const size_t nb = static_cast<size_t>(c.nbox) * c.B;
   hipError_t e = hipMalloc(&s->P, kSurBlob * sizeof(float));
-  if (!e) e = hipMalloc(&s->part, mlp_part_floats() * sizeof(float));
   if (!e) e = hipMalloc(&s->m, kSurParams * sizeof(float));
   if (!e) e = hipMalloc(&s->v, kSurParams * sizeof(float));
   if (!e) e = hipMalloc(&s->loss, sizeof(float));
@@ -85,6 +84,19 @@ int need_loaded(Ctx* c) {
   if (!c) return set_error(PM_NU_EINVAL, "ctx is NULL");
   if (!c->sur || !c->sur->loaded)
     return set_error(PM_NU_ESURROGATE, "no surrogate weights (load or init first)");
+  return PM_NU_OK;
+}
+
+// The gradient's sums (36 MB) belong to the first training or gradient call: a context that only
+// applies the network does without.
+int ensure_part(Ctx& c) {
+  Surrogate* s = c.sur;
+  if (s->part) return PM_NU_OK;
+  const hipError_t e = hipMalloc(&s->part, mlp_part_floats() * sizeof(float));
+  if (e != hipSuccess) {
+    s->part = nullptr;
+    return set_error(PM_NU_ENOMEM, "gradient workspace: %s", hipGetErrorString(e));
+  }
   return PM_NU_OK;
 }
 
@@ -216,6 +228,8 @@ int pm_nu_surrogate_train_part(pm_nu_ctx* ctx, const float* x, const float* y, i
     return set_error(PM_NU_EINVAL, "bad training arguments");
   if (n > (1ll << 31) - 1) return set_error(PM_NU_EINVAL, "too many rows");
   Surrogate* s = c->sur;
+  rc = ensure_part(*c);
+  if (rc) return rc;
   if (s->perm_cap < n) {
     if (s->perm) (void)hipFree(s->perm);
     s->perm = nullptr;
@@ -281,6 +295,8 @@ int pm_nu_surrogate_grad(pm_nu_ctx* ctx, const float* x, const float* y, int64_t
   if (rc) return rc;
   if (!x || !y || !grad || n < 1) return set_error(PM_NU_EINVAL, "bad arguments");
   Surrogate* s = c->sur;
+  rc = ensure_part(*c);
+  if (rc) return rc;
   int n_part = 0;
   SUR_LAUNCH(launch_mlp_train(s->P, s->packed, x, y, nullptr, 0, n, 1.0f / n, s->part, &n_part,
                               c->stream));
