@@ -74,7 +74,10 @@ void pm_nu_default_config(pm_nu_config* cfg);
 
 /* Create a context on the current HIP device. m_nu_total (host) [n_boxes]: total
  * neutrino mass per box in eV (0 allowed: plain CDM). Allocates every buffer the step
- * needs; later calls allocate nothing on the device (sync). */
+ * needs; later calls allocate nothing on the device, the surrogate's aside (sync). About 52
+ * bytes a mesh node, and the patch deposit's reserve: 18 bytes a particle, or, up to 64 MiB and
+ * where it is the default also up to an eighth of the memory then free, 52 (up to 78 a mesh
+ * node for sparse particles) for slots that hold wider chunks (pm_nu_set_launch). */
 int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** out);
 
 /* Release everything owned by ctx (sync). NULL is ignored. */
@@ -160,7 +163,7 @@ int pm_nu_binned_power_noalloc(const float* pos, int64_t n_particles, int n_mesh
 /* ---- diagnostics (copies of internal state, enqueued on the stream) ---------------- */
 /* (sync) How many chunk parts the patch deposit (deposit modes 6..9) has sent through its
  * atomic side grid since the last call (a chunk whose bounding box exceeds a patch's 26624
- * nodes, or its part in a coarse cell whose patch list was full); 0 when every chunk went
+ * or, in a context with the small reserve, 9216 nodes, or its part in a coarse cell whose patch list was full); 0 when every chunk went
  * through its patch, and always 0 for the other deposit modes. */
 int pm_nu_side_grid_uses(pm_nu_ctx* ctx, int64_t* uses);
 /* Deposited mass rho (unit mass per particle) of one box into out (dev) [N][N][N].
@@ -250,8 +253,9 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
  * particles on 256 threads, 4096 on 512 threads, 8192 on 1024 threads, flushed with global
  * atomics; mode 4 takes 512 on 256 threads for N <= 32 and for few particles), 6 (chunks of 4096, or 2048 or 1024 where
  * particles are sparse, written to per-chunk patches and summed per 16^3 coarse cell without atomics; a box beyond the LDS tile's 6144 nodes takes several
- * passes; a chunk whose box exceeds 26624 nodes, or its part in a coarse cell already listing
- * 32 patches, goes through atomics on a side grid),
+ * passes; a chunk whose box exceeds 26624 nodes (9216, and chunks of 4096 only, with the small
+ * reserve of pm_nu_init), or its part in a coarse cell already listing 32 patches, goes through
+ * atomics on a side grid),
  * 7 (as 6 with a tile of 9216 nodes, at lower occupancy), 8 and 9 (as 6 and 7 with
  * the coarse-cell sums and the first forward FFT pass in one kernel, so that delta never
  * goes to HBM; N >= 32), interp_mode

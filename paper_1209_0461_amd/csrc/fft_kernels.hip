@@ -1610,11 +1610,12 @@ template <int N> struct PatchFwdZ {
     }
   }
 };
-hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const int* reg_count,
+hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, int slot,
+                              const int* reg_count,
                               const int4* reg_list, unsigned long long* rho_fb, const int* n_fb,
                               float2* out, const float2* tw, double scale, int nbox,
                               hipStream_t s, float* delta_out) {
-  return dispatch_n<PatchFwdZ>(n, patches, kPatchSlot, reg_count, reg_list, rho_fb, n_fb, out, tw,
+  return dispatch_n<PatchFwdZ>(n, patches, slot, reg_count, reg_list, rho_fb, n_fb, out, tw,
                                scale, nbox, s, delta_out);
 }
 hipError_t launch_fwd_x_bin(int n, float2* data, const float2* tw, const uint16_t* bin_of_n2,

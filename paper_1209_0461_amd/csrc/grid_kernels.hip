@@ -489,7 +489,7 @@ __global__ __launch_bounds__(NT) void deposit_tiled_kernel(const float* __restri
 // every coarse cell (CB^3 nodes) that the box overlaps; a registry entry carries everything
 // D2 needs (chunk, box origin, extents). A box larger than the tile is summed in passes over
 // as many of its x-planes as fit, the particles staying in registers, up to the slot's
-// kPatchSlot nodes. D2: one workgroup per slab of a coarse cell adds up the registered patches
+// pcap nodes. D2: one workgroup per slab of a coarse cell adds up the registered patches
 // in exact integers and writes delta = rho / rho_bar - 1 once, rounded to FP32. Weights that
 // cannot go through a patch (a box too large: the whole chunk; a coarse cell whose list is
 // full: the box's part in that cell) are added with global atomics to a side grid kept at
@@ -504,7 +504,7 @@ __device__ __forceinline__ int ceil_div_pow2(int a, int lg) { return (a + (1 << 
 // displacements of 1 and 2 cells 1555 -> 102 and 3600 -> 132, C order 803 -> 166.
 template <int CH, int CAP, int NT>
 __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 2) void deposit_patch_kernel(
-    const float* __restrict__ pos, unsigned long long* __restrict__ patches,
+    const float* __restrict__ pos, unsigned long long* __restrict__ patches, int pcap,
     int* __restrict__ reg_count, int4* __restrict__ reg_list,
     unsigned long long* __restrict__ rho_fb, int* __restrict__ n_fb,
     int64_t np, int n, double inv_cell, int* __restrict__ flags, int64_t chunks_per_box,
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 
   const int rx = min(nc, ceil_div_pow2((gx0 & cbm) + ex, cb_lg));
   const int ry = min(nc, ceil_div_pow2((gy0 & cbm) + ey, cb_lg));
   const int rz = min(nc, ceil_div_pow2((gz0 & cbm) + ez, cb_lg));
-  const bool patch = npl > 0 && vol <= kPatchSlot && rx * ry * rz <= kPatchRegMax;
+  const bool patch = npl > 0 && vol <= pcap && rx * ry * rz <= kPatchRegMax;
   bool side = true;                    // something of the chunk goes to the side grid
   if (patch || (npl > 0 && vol <= kSideBoxMax)) {
     if (patch) {
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 
           atomicOr(&s_over[t >> 5], 1u << (t & 31));   // t < kPatchRegMax
       }
     }
-    unsigned long long* pat = patches + chunk * kPatchSlot;
+    unsigned long long* pat = patches + chunk * pcap;
     for (int p0 = 0; p0 < ex; p0 += npl) {
       const int npp = min(npl, ex - p0);
       clear_tile<NT>(tile, npp * sy * sz);
@@ -1157,36 +1157,22 @@ int64_t patch_coarse_cells(int n) {
   const int64_t nc = n >> patch_cb_log2(n);
   return nc * nc * nc;
 }
-// Particles a chunk of the patch deposit: a chunk of 4096 of sparse particles spans a box beyond
-// the patch slot's 26624 nodes as soon as it straddles two blocks of the curve, and goes through
-// atomics. A step, us, with 4096 / 2048 / 1024: 256^3 mesh with 128^3 particles 644 / 425 / 421,
-// 154^3 645 / 565 / 559, 180^3 693 / 575 / 554, 200^3 503 / 498 / 516, 220^3 748 / 651 / 656; 512^3
-// with 310^3 5126 / 4468 / 4193; 64 boxes of 64^3 with 40^3 587 / 392 / 375. Nearer a particle a
-// node smaller chunks lose (more halo): 256^3 with 240^3 517 / 530, 256^3 526 / 540. So 1024 up
-// to 3/8 of a particle a node, 2048 up to 3/4.
-int patch_chunk_particles(int64_t np, int n) {
-  const int64_t m = static_cast<int64_t>(n) * n * n;
-  return 8 * np <= 3 * m ? 1024 : 4 * np <= 3 * m ? 2048 : kPatchCH;
-}
-int64_t patch_chunks(int64_t np, int n) {
-  const int ch = patch_chunk_particles(np, n);
-  return (np + ch - 1) / ch;
-}
 
-hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, int* reg_count,
-                                int4* reg_list, unsigned long long* rho_fb, int* n_fb,
+hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches,
+                                const PatchLayout& layout, int* reg_count, int4* reg_list,
+                                unsigned long long* rho_fb, int* n_fb,
                                 int64_t np, int nbox, int n, double inv_cell, int* flags,
                                 bool big_tile, hipStream_t s) {
   if (n > 1024) return hipErrorInvalidValue;     // registry entries pack indices in 10 bits
-  const int64_t chunks = patch_chunks(np, n);
+  const int64_t chunks = layout.chunks;
   const dim3 grid(static_cast<unsigned>(chunks * nbox));
-  const int ch = patch_chunk_particles(np, n);
+  const int ch = layout.particles;
   const auto launch = [&](auto tile) {
     constexpr int TILE = decltype(tile)::value;
     const auto go = [&](auto part) {
       hipLaunchKernelGGL((deposit_patch_kernel<decltype(part)::value, TILE, kPatchNT>), grid,
-                         dim3(kPatchNT), 0, s, pos, patches, reg_count, reg_list, rho_fb, n_fb, np,
-                         n, inv_cell, flags, chunks, patch_cb_log2(n));
+                         dim3(kPatchNT), 0, s, pos, patches, layout.slot, reg_count, reg_list,
+                         rho_fb, n_fb, np, n, inv_cell, flags, chunks, patch_cb_log2(n));
     };
     if (ch == kPatchCH) go(std::integral_constant<int, kPatchCH>{});
     else if (ch == 2048) go(std::integral_constant<int, 2048>{});
@@ -1200,7 +1186,7 @@ hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, i
   return hipGetLastError();
 }
 
-hipError_t launch_patch_reduce(const unsigned long long* patches, const int* reg_count,
+hipError_t launch_patch_reduce(const unsigned long long* patches, int slot, const int* reg_count,
                                const int4* reg_list, unsigned long long* rho_fb,
                                const int* n_fb, float* delta, int nbox, int n, double scale,
                                hipStream_t s) {
@@ -1210,7 +1196,7 @@ hipError_t launch_patch_reduce(const unsigned long long* patches, const int* reg
   const auto launch = [&](auto xd) {
     constexpr int XD = decltype(xd)::value;
     hipLaunchKernelGGL(patch_reduce_kernel<XD>, dim3(static_cast<unsigned>(cells * (cb / XD)), nbox),
-                       dim3(256), 0, s, patches, kPatchSlot, reg_count, reg_list, rho_fb, n_fb,
+                       dim3(256), 0, s, patches, slot, reg_count, reg_list, rho_fb, n_fb,
                        delta, n, patch_cb_log2(n), scale);
   };
   if (static_cast<int64_t>(cells) * (cb / 8) * nbox < 512) launch(std::integral_constant<int, 2>{});

@@ -352,18 +352,18 @@ int do_deposit(Ctx& c, const float* pos) {
   if (c.tune.deposit_mode >= 6) {
     const bool big = c.tune.deposit_mode == 7 || c.tune.deposit_mode == 9;
     TIMED(c, ST_DEPOSIT,
-          launch_deposit_patch(pos, c.patches, c.reg_count, c.reg_list, c.rho_fb, c.n_fb,
-                               c.Np, c.nbox, c.N, inv_cell, c.d_flags, big, c.stream));
+          launch_deposit_patch(pos, c.patches, c.patch, c.reg_count, c.reg_list, c.rho_fb,
+                               c.n_fb, c.Np, c.nbox, c.N, inv_cell, c.d_flags, big, c.stream));
     if (fused) {
       // the patch sums and the z pass in one kernel; fwd_y resets the registry
       TIMED(c, ST_PATCH_FWD_Z,
-            launch_patch_fwd_z(c.N, c.patches, c.reg_count, c.reg_list, c.rho_fb, c.n_fb,
-                               c.ck[1], c.tw, scale, c.nbox, c.stream,
+            launch_patch_fwd_z(c.N, c.patches, c.patch.slot, c.reg_count, c.reg_list, c.rho_fb,
+                               c.n_fb, c.ck[1], c.tw, scale, c.nbox, c.stream,
                                c.keep_density ? c.delta : nullptr));
     } else {
       TIMED(c, ST_PATCH_REDUCE,
-            launch_patch_reduce(c.patches, c.reg_count, c.reg_list, c.rho_fb, c.n_fb, c.delta,
-                                c.nbox, c.N, scale, c.stream));
+            launch_patch_reduce(c.patches, c.patch.slot, c.reg_count, c.reg_list, c.rho_fb,
+                                c.n_fb, c.delta, c.nbox, c.N, scale, c.stream));
       if (zy)
         TIMED(c, ST_FWD_ZY, launch_fwd_zy(c.N, nullptr, c.delta, c.n_fb, c.reg_count, n_cells,
                                           c.ck[0], c.tw, scale, c.nbox, c.stream));
@@ -633,9 +633,7 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   ALLOC(c->inv_w2, static_cast<size_t>(c->N));
   ALLOC(c->d_flags, 1);
   {
-    const size_t chunks = nb * static_cast<size_t>(patch_chunks(c->Np, c->N));
     const size_t coarse = nb * static_cast<size_t>(patch_coarse_cells(c->N));
-    ALLOC(c->patches, chunks * kPatchSlot);
     ALLOC(c->reg_count, coarse);
     ALLOC(c->reg_list, coarse * 32);
     ALLOC(c->rho_fb, nb * c->M);
@@ -644,7 +642,6 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
     ALLOC(c->delta, nb * c->M);
   }
   ALLOC(c->d_kd, 2 * nb);
-#undef ALLOC
   // the pinned staging in one allocation (each costs about 0.1 ms)
   const size_t n_tg = 3 * nb * c->qcap * sizeof(double), n_resp = nb * sizeof(RespBox),
                n_kd = 2 * nb * sizeof(double), n_spec = (3 * B + 1) * sizeof(double);
@@ -659,6 +656,20 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   c->h_kd = reinterpret_cast<double*>(pinned + n_tg + n_resp);
   c->h_spec = reinterpret_cast<double*>(pinned + n_tg + n_resp + n_kd);
   c->h_up = reinterpret_cast<uint32_t*>(pinned + n_tg + n_resp + n_kd + n_spec);
+  // the patches last, when the rest of the context has its memory
+  c->patch = patch_layout(c->Np, c->N, true);
+  bool wide = patch_wide_fits(c->patch.bytes(c->nbox), false, 0);
+  if (!wide && c->tune.deposit_mode >= 6) {
+    size_t free_bytes = 0, total_bytes = 0;
+    wide = hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess &&
+           patch_wide_fits(c->patch.bytes(c->nbox), true, static_cast<int64_t>(free_bytes));
+  }
+  if (!wide || hipMalloc(reinterpret_cast<void**>(&c->patches), c->patch.bytes(c->nbox)) != hipSuccess) {
+    (void)hipGetLastError();
+    c->patch = patch_layout(c->Np, c->N, false);
+    ALLOC(c->patches, c->patch.bytes(c->nbox) / sizeof(unsigned long long));
+  }
+#undef ALLOC
   std::memset(c->h_tg, 0, 3 * nb * c->qcap * sizeof(double));
   *c->h_up = 0;
   c->tgc.resize(c->nbox);

@@ -10,6 +10,7 @@
 
 #include "../../include/pm_nu.h"
 #include "host_consts.hpp"
+#include "patch_layout.hpp"
 #include "surrogate_layout.hpp"
 
 namespace pmnu {
@@ -168,7 +169,8 @@ struct Ctx {
   float* inv_w2 = nullptr;         // [N] 1/sinc^4(pi n/N) per axis index (or 1)
   int* d_flags = nullptr;          // [1] bit 0: non-finite position seen
   // patch deposit (deposit modes 6 and 7)
-  unsigned long long* patches = nullptr;   // [chunks][kPatchSlot] per-chunk patches
+  unsigned long long* patches = nullptr;   // [nbox][patch.chunks][patch.slot] per-chunk patches
+  PatchLayout patch;
   int* reg_count = nullptr;        // [nbox][coarse cells] patches registered
   int4* reg_list = nullptr;        // [nbox][coarse cells][32] (chunk, origin, extents, 0)
   unsigned long long* rho_fb = nullptr;    // [nbox][M] side grid, kept at zero
@@ -247,13 +249,8 @@ void surrogate_free(Ctx& c);
 constexpr double kFixScale = 1099511627776.0;   // 2^40: fixed-point unit of the deposit
 constexpr int kMaxBins = 1024;                   // largest n_kbins
 static_assert(kMaxBins <= (1 << kRatioBinBits), "bin index of the packed ratio index");
-// patch deposit: chunks of kPatchCH particles on kPatchNT threads; the LDS tile holds
-// kPatchTile nodes (mode 6, three workgroups per CU) or kPatchCap (mode 7, two); a stored
-// patch has room for kPatchSlot nodes, summed in several passes beyond the tile: a 16^3 block
-// whose halo is six nodes a side (28^3), or 16 rows of 256 particles in C order (5 x 20 x 256)
-constexpr int kPatchCH = 4096, kPatchCap = 9216, kPatchTile = 6144, kPatchNT = 512;
+// patch deposit (patch_layout.hpp): chunks on kPatchNT threads
 constexpr int kPatchPad = 448;       // more room in the tile for padded strides (18 x 18 x 20)
-constexpr int kPatchSlot = 26624;
 // up to one chunk per CU a workgroup has a CU to itself and takes most of its LDS
 constexpr int kPatchFewChunks = 256, kPatchFewTile = 18432;
 // largest box that goes to the side grid node by node: 8 nodes a particle, what the particles
@@ -293,7 +290,8 @@ hipError_t launch_fwd_zy(int N, unsigned long long* rho, float* delta, int* rese
                          int nbox, hipStream_t s, float* rho_out = nullptr);
 // the patch sums and the first (z) forward pass in one kernel (N >= 32); delta_out, when
 // given, also receives delta
-hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, const int* reg_count,
+hipError_t launch_patch_fwd_z(int n, const unsigned long long* patches, int slot,
+                              const int* reg_count,
                               const int4* reg_list, unsigned long long* rho_fb, const int* n_fb,
                               float2* out, const float2* tw, double scale, int nbox,
                               hipStream_t s, float* delta_out);
@@ -371,16 +369,14 @@ hipError_t launch_surrogate_dataset(const RespBox* boxes, const double* pcdm, co
                                     float* x, float* y, hipStream_t s);
 int patch_cb_log2(int n);
 int64_t patch_coarse_cells(int n);
-// particles a chunk of the patch deposit, and its chunks
-int patch_chunk_particles(int64_t np, int n);
-int64_t patch_chunks(int64_t np, int n);
 // big_tile: the kPatchCap-node LDS tile (mode 7) instead of kPatchTile (mode 6); reg_list
 // entries are (chunk, packed box origin, packed extents, 0), n <= 1024
-hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches, int* reg_count,
-                                int4* reg_list, unsigned long long* rho_fb, int* n_fb,
+hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches,
+                                const PatchLayout& layout, int* reg_count, int4* reg_list,
+                                unsigned long long* rho_fb, int* n_fb,
                                 int64_t np, int nbox, int n, double inv_cell, int* flags,
                                 bool big_tile, hipStream_t s);
-hipError_t launch_patch_reduce(const unsigned long long* patches, const int* reg_count,
+hipError_t launch_patch_reduce(const unsigned long long* patches, int slot, const int* reg_count,
                                const int4* reg_list, unsigned long long* rho_fb,
                                const int* n_fb, float* delta, int nbox, int n, double scale,
                                hipStream_t s);
