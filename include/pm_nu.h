@@ -244,8 +244,9 @@ int pm_nu_advance(pm_nu_ctx* ctx, float* pos, float* vel, float* acc, const doub
  * HIP events (pos/acc (dev) as for pm_nu_step, a_now as for pm_nu_response; the history
  * must be set): the deposit mode and block, the interpolation mode and block, and the three
  * tile candidates of each FFT pass (pm_nu_set_fft_tiles); keep the fastest of each, and if
- * cache_path is not NULL read/write the choice as JSON keyed by (device architecture, N,
- * n_boxes, particles per box) (sync). Ends with one full step at a_now. */
+ * cache_path is not NULL read/write the choice as JSON keyed by (device architecture, version of
+ * the candidates, N, n_boxes, particles per box) (sync); a line of another version is timed
+ * again. Ends with one full step at a_now. */
 int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
                    const char* cache_path);
 /* Set the launch shapes directly: deposit_mode 0 (one thread per particle, global atomics;

@@ -2,7 +2,7 @@
 // deposit's chunking mode / block size, the interpolation's mode / block size) and the tile
 // candidates of the six FFT passes with HIP events on the context's own buffers and keeps
 // the fastest of each; the choice can be cached as JSON lines keyed by (device
-// architecture, N, n_boxes, particles per box).
+// architecture, version of the candidates, N, n_boxes, particles per box).
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -19,12 +19,17 @@ using namespace pmnu;
 
 namespace {
 
+// Raised whenever a stored number comes to mean another shape (a tile table, the kernel behind a
+// mode): lines of other versions are timed again. Lines before the first had no version; N = 64
+// (fwd_x, inv_x) and N = 512 (inv_y) have other tiles since, and modes 4 and 6 to 9 other kernels.
+constexpr int kCandidates = 2;
+
 std::string cache_key(const Ctx& c) {
   hipDeviceProp_t prop;
   std::string dev = "unknown";
   if (hipGetDeviceProperties(&prop, c.device) == hipSuccess) dev = prop.gcnArchName;
   std::ostringstream o;
-  o << dev << "/N" << c.N << "/boxes" << c.nbox << "/np" << c.Np;
+  o << dev << "/v" << kCandidates << "/N" << c.N << "/boxes" << c.nbox << "/np" << c.Np;
   return o.str();
 }
 
