@@ -207,12 +207,13 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
       const float ms = time_ms([&](bool prep) -> hipError_t {
         if (prep) return hipSuccess;
         switch (p) {
-          case 0:   // the density as the step's deposit left it (delta or the fixed-point sum)
+          case 0:   // delta as the step's deposit left it, or the fixed-point mesh, which that
+                    // step left cleared, with the FP32 density stored and the mesh cleared again
             return c->density_is_delta
                        ? launch_fwd_z(c->N, nullptr, c->delta, nullptr, nullptr, 0, c->ck[2],
                                       c->tw, scale, c->nbox, c->stream, v)
                        : launch_fwd_z(c->N, c->rho, nullptr, nullptr, nullptr, 0, c->ck[2],
-                                      c->tw, scale, c->nbox, c->stream, v);
+                                      c->tw, scale, c->nbox, c->stream, v, c->delta);
           case 1: return launch_fwd_y(c->N, c->ck[1], c->ck[2], c->tw, c->nbox, c->stream, v);
           case 2:
             return launch_fwd_x_bin(c->N, c->ck[0], c->tw, c->bin_of_n2, c->d_edges, c->bin_partial,

@@ -47,3 +47,27 @@ def test_line_without_this_version_is_timed_again(tmp_path):
     after = _lines(cache)
     assert [l["key"] for l in after] == old_keys + [new["key"]]   # lines of others are kept
     assert after[-1]["fft"] == got["fft"]
+
+
+@pytest.mark.parametrize("n_mesh,n_part", [(32, 3000), (256, 20000)])
+def test_density_after_tuning(n_mesh, n_part):
+    """The tuner leaves a whole step's density whatever it stored while it timed the passes, and a
+    cleared mesh for the next deposit by atomics."""
+    import torch
+    from paper_1209_0461_amd import binding
+    pos = torch.rand((n_part, 3), device="cuda") * 100.0
+    acc = torch.zeros_like(pos)
+    rho = [torch.empty((n_mesh,) * 3, device="cuda") for _ in range(3)]
+    ctx = _context(n_mesh, n_part)
+    binding.pm_nu_set_keep_density(ctx.h, 1)
+    binding.pm_nu_autotune(ctx.h, pos, acc, 0.2, None)
+    binding.pm_nu_copy_density(ctx.h, 0, rho[0])
+    for r, mode in ((rho[1], 4), (rho[2], 0)):
+        binding.pm_nu_set_launch(ctx.h, mode, 256, 0, 256)
+        ctx.deposit(pos)
+        binding.pm_nu_copy_density(ctx.h, 0, r)
+    torch.cuda.synchronize()
+    ctx.close()
+    assert torch.equal(rho[1], rho[2])
+    # modes 6..9 keep delta in FP32: a node is off by at most 5 roundings of 2^-24
+    assert (rho[0].double() - rho[1].double()).abs().max() <= 2.0 ** -21 * rho[1].max()
