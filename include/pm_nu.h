@@ -257,7 +257,8 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
  * passes; a chunk whose box exceeds 26624 nodes (9216, and chunks of 4096 only, with the small
  * reserve of pm_nu_init), or its part in a coarse cell already listing 32 patches, goes through
  * atomics on a side grid),
- * 7 (as 6 with a tile of 9216 nodes, at lower occupancy), 8 and 9 (as 6 and 7 with
+ * 7 (as 6 with a tile of 9216 nodes, at lower occupancy; up to 256 chunks in all, modes 6 to 9
+ * have a tile of 18432 nodes and 7 and 9 are 6 and 8), 8 and 9 (as 6 and 7 with
  * the coarse-cell sums and the first forward FFT pass in one kernel, so that delta never
  * goes to HBM; N >= 32), interp_mode
  * 0 (direct gather; interp_block = particles per workgroup, rounded down to 256, 512 or

@@ -159,6 +159,8 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
   // the deposit candidates are timed as whole deposits (including the forward transform)
   // since the patch mode replaces the zero pass and changes what the first FFT pass reads
   for (const DepCand& d : dep) {
+    // few chunks take the same tile in modes 6 and 7, and in 8 and 9
+    if ((d.mode == 7 || d.mode == 9) && c->patch.chunks * c->nbox <= kPatchFewChunks) continue;
     c->tune.deposit_mode = d.mode;
     c->tune.deposit_block = d.block;
     float ms = 0.f;

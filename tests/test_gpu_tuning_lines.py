@@ -71,3 +71,19 @@ def test_density_after_tuning(n_mesh, n_part):
     assert torch.equal(rho[1], rho[2])
     # modes 6..9 keep delta in FP32: a node is off by at most 5 roundings of 2^-24
     assert (rho[0].double() - rho[1].double()).abs().max() <= 2.0 ** -21 * rho[1].max()
+
+
+def test_modes_that_are_the_same_kernel_are_timed_once():
+    """256 chunks: modes 7 and 9 launch what 6 and 8 launch, so the tuner never names them."""
+    import torch
+    from paper_1209_0461_amd import binding
+    n_mesh, n_part = 128, 262000
+    pos = torch.rand((n_part, 3), device="cuda") * 100.0
+    cell = (pos / 12.5).floor().long()
+    pos = pos[torch.argsort((cell[:, 0] * 8 + cell[:, 1]) * 8 + cell[:, 2])].contiguous()
+    acc = torch.zeros_like(pos)
+    for _ in range(6):
+        ctx = _context(n_mesh, n_part)
+        binding.pm_nu_autotune(ctx.h, pos, acc, 0.2, None)
+        assert json.loads(binding.pm_nu_tuning(ctx.h))["deposit_mode"] not in (7, 9)
+        ctx.close()
