@@ -252,9 +252,10 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
 /* Set the launch shapes directly: deposit_mode 0 (one thread per particle, global atomics;
  * deposit_block = threads per workgroup), 1..5 (LDS-privatised chunks of 1024/2048/4096
  * particles on 256 threads, 4096 on 512 threads, 8192 on 1024 threads, flushed with global
- * atomics; mode 4 takes 512 on 256 threads for N <= 32 and for few particles), 6 (chunks of 4096, or 2048 or 1024 where
- * particles are sparse, written to per-chunk patches and summed per 16^3 coarse cell without atomics; a box beyond the LDS tile's 6144 nodes takes several
- * passes; a chunk whose box exceeds 26624 nodes (9216, and chunks of 4096 only, with the small
+ * atomics; mode 4 takes 512 on 256 threads for few particles and on small meshes, 4096 on 256
+ * threads for many on meshes up to 32^3), 6 (chunks of 4096, or 2048 or 1024 where particles are
+ * sparse, written to per-chunk patches and summed per 16^3 coarse cell without atomics; a box
+ * beyond the LDS tile's 6144 nodes takes several passes; a chunk whose box exceeds 26624 nodes (9216, and chunks of 4096 only, with the small
  * reserve of pm_nu_init), or its part in a coarse cell already listing 32 patches, goes through
  * atomics on a side grid),
  * 7 (as 6 with a tile of 9216 nodes, at lower occupancy; up to 256 chunks in all, modes 6 to 9
@@ -265,7 +266,7 @@ int pm_nu_autotune(pm_nu_ctx* ctx, const float* pos, float* acc, double a_now,
  * 1024) or 1/2/3 (LDS-staged chunks). Blocks: multiples of 64 in 64..1024. Until this or
  * pm_nu_autotune is called: deposit_mode 6 for N >= 64 (4 below, where one coarse cell
  * covers the mesh, and for few particles on small meshes), interp_mode 1 (0 up to 2^21
- * particles, or one for two nodes). */
+ * particles, or one for two nodes, or N <= 16). */
 int pm_nu_set_launch(pm_nu_ctx* ctx, int deposit_mode, int deposit_block, int interp_mode,
                      int interp_block);
 /* Tile candidates of the six FFT passes, candidates[6] (host) in the order fwd_z (real rows

@@ -1124,13 +1124,19 @@ hipError_t launch_tiled(const float* pos, unsigned long long* rho, int64_t np, i
 }
 
 // Mode 4 takes chunks of 512 particles on 256 threads where the 4096-particle chunks would
-// leave the chip idle, or a chunk would be most of a small mesh (boxes up to 32^3, whose tile
-// of a 16^3 block plus its halo is the mesh again for every chunk). A tile of 3328 nodes
-// (27 KB) holds an 8^3 block with a halo of three nodes a side. Deposit alone, us, 4096 -> 512
-// particles a chunk, Morton order: one 32^3 box 10.0 -> 5.0 (8 workgroups -> 64), one 64^3 box
-// 11.9 -> 9.4, 16 and 256 boxes of 32^3 28.9 -> 13.0 and 234 -> 123. From 512 chunks of 4096
-// on the larger chunk has fewer atomics to flush and wins (128^3: 30.5 against 36.1).
-constexpr int64_t kSmallDeposit = 512;
+// leave the chip idle, or a chunk would be most of a small mesh (boxes of 32^3, whose tile of a
+// 16^3 block plus its halo is the mesh again for every chunk). A tile of 3328 nodes (27 KB) holds
+// an 8^3 block with a halo of three nodes a side. Deposit alone, us, 4096 -> 512 particles a
+// chunk, Morton order: one 32^3 box 10.0 -> 5.0 (8 workgroups -> 64), one 64^3 box 11.9 -> 9.4,
+// 16 and 256 boxes of 32^3 28.9 -> 13.0 and 234 -> 123. From 512 chunks of 4096 on the larger
+// chunk has fewer atomics to flush and wins (128^3: 30.5 against 36.1); on meshes up to 32^3,
+// where many particles share a node, from 256 on, or at 32^3 from four a node on (a box of at
+// most 512 particles is one chunk either way and keeps the smaller tile). There 256 threads are
+// faster than 512 (64 boxes of 32^3 with 64^3 particles: 186 against 210). A step,
+// us, 512 a chunk / 4096 on 256 threads, Morton order: 8^3 with 128^3 particles 92 / 77, 64
+// boxes of 16^3 with 48^3 185 / 168, 32^3 with 200^3 202 / 188, 64 boxes of 32^3 with 32^3 125 /
+// 437, with 50^3 240 / 464, with 64^3 418 / 359.
+constexpr int64_t kSmallDeposit = 512, kSmallMeshDeposit = 256;
 // mode 0: one thread per particle, global atomics (`block` threads per workgroup);
 // modes 1-5: LDS-privatised chunks of 1024 / 2048 / 4096 particles with 256 threads, 4096
 // with 512 threads, 8192 with 1024 threads.
@@ -1140,10 +1146,14 @@ hipError_t launch_deposit(const float* pos, unsigned long long* rho, int64_t np,
     case 1: return launch_tiled<1024, 3328, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
     case 2: return launch_tiled<2048, 5120, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
     case 3: return launch_tiled<4096, 9216, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
-    case 4:
-      if (n <= 32 || (np + 4095) / 4096 * nbox < kSmallDeposit)
+    case 4: {
+      const int64_t chunks = (np + 4095) / 4096 * nbox;
+      if (chunks < (n <= 32 ? kSmallMeshDeposit : kSmallDeposit) || (n <= 32 && np <= 512) ||
+          (n == 32 && np < 4 * n * n * n))
         return launch_tiled<512, 3328, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
+      if (n <= 32) return launch_tiled<4096, 9216, 256>(pos, rho, np, nbox, n, inv_cell, flags, s);
       return launch_tiled<4096, 9216, 512>(pos, rho, np, nbox, n, inv_cell, flags, s);
+    }
     case 5: return launch_tiled<8192, 18432, 1024>(pos, rho, np, nbox, n, inv_cell, flags, s);
     default:
       hipLaunchKernelGGL(deposit_kernel, dim3(grid_blocks(np * nbox, block, 1)), dim3(block), 0,

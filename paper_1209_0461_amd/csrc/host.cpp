@@ -329,7 +329,9 @@ int default_deposit_mode(int n, int nbox, int64_t np) {
 //   - there are at most 2^21, whose force grid the caches hold while few workgroups cannot hide
 //     the three memory latencies of a staged box (512 a workgroup: 32^3 10.5 / 6.4, 64^3 10.6 /
 //     7.0, four 64^3 boxes 16.2 / 13.4, eight 22.7 / 21.7, 128^3 22.0 / 22.1, displaced by 1.5
-//     cells 24.7 / 22.9, in C order 22.6 / 15.8; 128 boxes of 32^3 35.6 / 38.0).
+//     cells 24.7 / 22.9, in C order 22.6 / 15.8; 128 boxes of 32^3 35.6 / 38.0);
+//   - the mesh has at most 16^3 nodes, where the staged box is most of a force grid of at most
+//     49 KB and its chunks wrap around the mesh (64 boxes of 16^3 with 48^3 particles 57 / 40).
 constexpr int64_t kDirectInterp = int64_t{1} << 21;
 
 // The stream is being captured, by pm_nu_graph_capture or by the caller.
@@ -577,7 +579,8 @@ int pm_nu_init(const pm_nu_config* cfg, const double* m_nu_total, pm_nu_ctx** ou
   for (int v = 1; v < 3; ++v) max_partial = std::max(max_partial, fwd_x_partials(c->N, v));
   c->n_partial_cap = max_partial;
   c->tune.deposit_mode = default_deposit_mode(c->N, c->nbox, c->Np);
-  c->tune.interp_mode = 2 * c->Np <= c->M || c->Np * c->nbox <= kDirectInterp ? 0 : 1;
+  c->tune.interp_mode =
+      2 * c->Np <= c->M || c->Np * c->nbox <= kDirectInterp || c->N <= 16 ? 0 : 1;
   c->tune.interp_block = 2 * c->Np <= c->M ? 256 : 512;
   c->stream = static_cast<hipStream_t>(cfg->stream);
   c->m_nu.assign(m_nu_total, m_nu_total + c->nbox);
