@@ -32,18 +32,16 @@ namespace {
 // for an FP32 coordinate times an FP64 inverse cell size up to the product's rounding).
 // The node index comes from adding 1.5 * 2^52, which leaves floor(u) in two's complement
 // in the low bits for |u| < 2^51; the mask keeps any index in range. (Beyond, the coordinate's own
-// spacing is more than a box; every deposit and interpolation takes the place found here.)
+// spacing is more than a box; every deposit and interpolation takes the node found here.)
 // The product is rounded by itself in every deposit (no fused multiply-subtract for the fraction,
 // which the compiler would form in some of them), so that all give the same fixed-point weights.
-__device__ __forceinline__ unsigned axis_bits(float x, double inv_cell, double& d) {
+constexpr double kFloorMagic = 6755399441055744.0;     // 1.5 * 2^52
+__device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int& i, double& d) {
 #pragma clang fp contract(off)
   const double u = static_cast<double>(x) * inv_cell;
   const double f = floor(u);
   d = u - f;
-  return static_cast<unsigned>(__double2loint(f + 6755399441055744.0));
-}
-__device__ __forceinline__ void axis64(float x, double inv_cell, int nmask, int& i, double& d) {
-  i = static_cast<int>(axis_bits(x, inv_cell, d)) & nmask;
+  i = static_cast<int>(__double2loint(f + kFloorMagic)) & nmask;
 }
 
 // The product a b, 0 <= a b < 2^52, rounded to the nearest integer (ties to even): adding 2^52
@@ -163,7 +161,7 @@ struct Chunk {
   float p[PPT][3];
   unsigned ok;
   int g0[3], ext[3];
-  bool any, full, bad;
+  bool full, bad;
 };
 struct ChunkRed {
   float m[7][16];   // per wave: -min and max of each axis, then a NaN mark
@@ -172,10 +170,11 @@ struct ChunkRed {
 
 // floor(x inv_cell) is monotone in x, so the box of a chunk that does not wrap around the
 // mesh is that of its smallest and largest coordinates: three v_min3 / v_max3 pairs for two
-// particles, where finding every particle's node took 12 instructions an axis. A chunk with
-// a non-finite coordinate, or whose nodes span half the mesh or more (it may wrap), takes the
-// nodes of every particle relative to the first one's instead; the two give the same box
-// where both apply. One barrier, two more in the second form.
+// particles, where finding every particle's node took 12 instructions an axis. A chunk whose
+// nodes span half the mesh or more (it may wrap) takes the nodes of every particle relative to
+// the first one's instead; the two give the same box where both apply. One barrier, one more in
+// the second form. A chunk with a coordinate that is not finite (which may hide others in the
+// extremes) or beyond 2^30 cells has the whole mesh for its box.
 template <int PPT, int NT>
 __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt, double inv_cell,
                                           int nmask, ChunkRed& red) {
@@ -221,43 +220,49 @@ __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt
   v = max8(v);
   const double u = floor(static_cast<double>(a8 < 3 ? -v : v) * inv_cell);
   const int node = fabs(u) < 1073741824.0 ? static_cast<int>(u) : 0x7fffffff;
-  bool fast = __builtin_amdgcn_readlane(__float_as_int(v), 48) == 0;
-  c.any = true;
+  bool near = __builtin_amdgcn_readlane(__float_as_int(v), 48) == 0, fast = true;
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const int lo = __builtin_amdgcn_readlane(node, 8 * a);
     const int hi = __builtin_amdgcn_readlane(node, 24 + 8 * a);
-    fast = fast && lo != 0x7fffffff && hi != 0x7fffffff && hi - lo < half;
+    near = near && lo != 0x7fffffff && hi != 0x7fffffff;
+    const int span = static_cast<int>(static_cast<unsigned>(hi) - static_cast<unsigned>(lo));
+    fast = fast && span < half;
     c.g0[a] = lo & nmask;
-    c.ext[a] = hi - lo + 2;
+    c.ext[a] = span + 2;                 // where it is taken at most half + 1 < n
   }
   c.ok = 0u;
+#pragma unroll
+  for (int q = 0; q < PPT; ++q) c.ok |= tid + q * NT < cnt ? 1u << q : 0u;
   c.bad = false;
   c.full = false;
-  if (fast) {
+  if (near && fast) return;
+  if (!near) {
 #pragma unroll
-    for (int q = 0; q < PPT; ++q) c.ok |= tid + q * NT < cnt ? 1u << q : 0u;
+    for (int q = 0; q < PPT; ++q) {
+      if (((c.ok >> q) & 1u) && !finite3(c.p[q][0], c.p[q][1], c.p[q][2])) {
+        c.bad = true;
+        c.ok &= ~(1u << q);
+      }
+    }
+    c.full = true;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) c.full = c.full || c.ext[a] >= n;   // n = 8: 5 + 2 never
+    for (int a = 0; a < 3; ++a) {
+      c.g0[a] = 0;
+      c.ext[a] = n;
+    }
     return;
   }
   int r[3];
-  {
-    const float x = p[0], y = p[1], z = p[2];
-    const bool ok0 = finite3(x, y, z);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
     double d;
-    axis64(ok0 ? x : 0.f, inv_cell, nmask, r[0], d);
-    axis64(ok0 ? y : 0.f, inv_cell, nmask, r[1], d);
-    axis64(ok0 ? z : 0.f, inv_cell, nmask, r[2], d);
+    axis64(p[a], inv_cell, nmask, r[a], d);
   }
   int in[3] = {1 << 30, 1 << 30, 1 << 30}, ix[3] = {-(1 << 30), -(1 << 30), -(1 << 30)};
 #pragma unroll
   for (int q = 0; q < PPT; ++q) {
-    const bool here = tid + q * NT < cnt;
-    const bool ok = here && finite3(c.p[q][0], c.p[q][1], c.p[q][2]);
-    c.bad |= here && !ok;
-    if (!ok) continue;
-    c.ok |= 1u << q;
+    if (!((c.ok >> q) & 1u)) continue;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       int i;
@@ -287,11 +292,7 @@ __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt
     }
     in[a] = __builtin_amdgcn_readfirstlane(in[a]);
     ix[a] = __builtin_amdgcn_readfirstlane(ix[a]);
-  }
-  c.any = in[0] <= ix[0];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    c.ext[a] = c.any ? ix[a] - in[a] + 2 : 0;
+    c.ext[a] = ix[a] - in[a] + 2;
     c.g0[a] = (__builtin_amdgcn_readfirstlane(r[a]) + in[a]) & nmask;
     if (c.ext[a] >= n) {
       c.ext[a] = n;
@@ -301,12 +302,16 @@ __device__ __forceinline__ void chunk_box(Chunk<PPT>& c, const float* p, int cnt
   }
 }
 
-// A particle's lower node relative to the box origin g0 and its fraction on one axis. g0 comes off
-// in integers: taken off the magic number instead, as one addition, it agrees with axis64 only
-// for |u| < 2^51, and the place of a finite coordinate beyond lay outside the box.
-__device__ __forceinline__ void box_axis(float x, double inv_cell, int g0, int nmask, int& t,
+// A particle's lower node relative to the box origin and its fraction on one axis; mg is
+// kFloorMagic - g0, so that the node comes out relative to g0 in one addition. That is axis64's node
+// less g0 only for |u| < 2^51 or g0 = 0: chunk_box gives chunks that may hold more the origin 0.
+__device__ __forceinline__ void box_axis(float x, double inv_cell, double mg, int nmask, int& t,
                                          double& d) {
-  t = static_cast<int>(axis_bits(x, inv_cell, d) - static_cast<unsigned>(g0)) & nmask;
+#pragma clang fp contract(off)               // as axis64
+  const double u = static_cast<double>(x) * inv_cell;
+  const double f = floor(u);
+  d = u - f;
+  t = static_cast<int>(__double2loint(f + mg)) & nmask;
 }
 
 // Strides of an ey x ez plane in an LDS tile: padded so that a wave's 16-lane groups of
@@ -341,20 +346,21 @@ __device__ __forceinline__ void add_chunk(const Chunk<PPT>& c, unsigned long lon
                                           double inv_cell, int nmask, int sy, int sz, int p0,
                                           int npl) {
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2], plane = sy * sz;
+  const double mx = kFloorMagic - c.g0[0], my = kFloorMagic - c.g0[1], mz = kFloorMagic - c.g0[2];
 #pragma unroll
   for (int q = 0; q < PPT; ++q) {
     if (!((c.ok >> q) & 1u)) continue;
     int t[3];
     double d[3];
-    box_axis(c.p[q][0], inv_cell, c.g0[0], nmask, t[0], d[0]);
+    box_axis(c.p[q][0], inv_cell, mx, nmask, t[0], d[0]);
     if constexpr (!WHOLE) {
       const int up = t[0] + 1 < ex ? t[0] + 1 : 0;
       if (static_cast<unsigned>(t[0] - p0) >= static_cast<unsigned>(npl) &&
           static_cast<unsigned>(up - p0) >= static_cast<unsigned>(npl))
         continue;
     }
-    box_axis(c.p[q][1], inv_cell, c.g0[1], nmask, t[1], d[1]);
-    box_axis(c.p[q][2], inv_cell, c.g0[2], nmask, t[2], d[2]);
+    box_axis(c.p[q][1], inv_cell, my, nmask, t[1], d[1]);
+    box_axis(c.p[q][2], inv_cell, mz, nmask, t[2], d[2]);
     const double wx[2] = {(1.0 - d[0]) * kFixScale, d[0] * kFixScale};
     const double wy[2] = {1.0 - d[1], d[1]};
     const double wz[2] = {1.0 - d[2], d[2]};
@@ -465,7 +471,7 @@ __global__ __launch_bounds__(NT) void deposit_tiled_kernel(const float* __restri
   if (c.bad) atomicOr(flags, 1);
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2];
   const TileStrides ts = tile_strides(ex, ey, ez, CAP);
-  if (c.any && ts.npl == ex) {
+  if (ts.npl == ex) {
     clear_tile<NT>(tile, ex * ts.sy * ts.sz);
     __syncthreads();
     if (c.full) add_chunk<false>(c, tile, inv_cell, nmask, ts.sy, ts.sz, 0, ex);
@@ -531,7 +537,7 @@ __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 
   const int plane = ey * ez, vol = ex * plane;         // < 2^28
   const int gx0 = c.g0[0], gy0 = c.g0[1], gz0 = c.g0[2];
   const TileStrides ts = tile_strides(ex, ey, ez, TILE);
-  const int sy = ts.sy, sz = ts.sz, npl = c.any ? ts.npl : 0;   // npl: planes per pass
+  const int sy = ts.sy, sz = ts.sz, npl = ts.npl;      // npl: planes per pass
   const int nc = n >> cb_lg, cbm = (1 << cb_lg) - 1;
   const int rx = min(nc, ceil_div_pow2((gx0 & cbm) + ex, cb_lg));
   const int ry = min(nc, ceil_div_pow2((gy0 & cbm) + ey, cb_lg));
@@ -975,7 +981,7 @@ __global__ __launch_bounds__(256, CH <= 1024 ? 6 : 1) void interp_tiled_kernel(c
   chunk_box<PPT, 256>(c, pos + (box * np + c0) * 3, cnt, inv_cell, nmask, red);
   const int ex = c.ext[0], ey = c.ext[1], ez = c.ext[2];
   const int vol = ex * ey * ez;
-  const bool use_tile = c.any && vol <= CAP && !c.full;
+  const bool use_tile = vol <= CAP && !c.full;
   // every particle's node in the box (three 10-bit fields) and fraction
   int rel[PPT];
   float fr[PPT][3];
@@ -986,7 +992,7 @@ __global__ __launch_bounds__(256, CH <= 1024 ? 6 : 1) void interp_tiled_kernel(c
     for (int a = 0; a < 3; ++a) {
       int t;
       double d;
-      box_axis(c.p[q][a], inv_cell, c.g0[a], nmask, t, d);
+      box_axis(c.p[q][a], inv_cell, kFloorMagic - c.g0[a], nmask, t, d);
       rel[q] |= t << (10 * a);
       fr[q][a] = static_cast<float>(d);
     }

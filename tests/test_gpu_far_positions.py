@@ -65,3 +65,24 @@ def test_far_coordinates(n_mesh, where):
             assert torch.equal(got, delta), mode
             bar = len(pos) / n_mesh ** 3
             assert (got.double() - rho.double()).abs().max() <= 2.0 ** -21 * (rho.max() + bar)
+
+
+@pytest.mark.parametrize("n_mesh", [16, 64])
+@pytest.mark.parametrize("hide", [np.nan, np.inf, -np.inf])
+def test_far_coordinates_beside_skipped_particles(n_mesh, hide):
+    """Particles that are skipped must not hide a far one of their wave or chunk."""
+    pos = _positions(n_mesh, "alone")
+    n = len(pos)
+    for start, count, axis in ((0, 1, 0), (640, 128, 1), (4096, 64, 2), (4199, 3, 0), (8192, 4096, 1)):
+        keep = pos[start:start + count:5].clone()
+        pos[start:start + count, axis] = float(hide)
+        pos[start:start + count:5] = keep
+    bad = ~torch.isfinite(pos).all(dim=1)
+    assert 0 < int(bad.sum()) < n and (pos[~bad].abs() > 1e9).any()
+    rho, acc = _step(pos, n_mesh, 0, 0)
+    assert abs(rho.double().sum().item() / (n - int(bad.sum())) - 1.0) <= 2.0 ** -24
+    assert (acc[bad] == 0).all() and torch.isfinite(acc).all()
+    for mode in range(1, 8):
+        got, a = _step(pos, n_mesh, mode, (mode - 1) % 3 + 1)
+        assert torch.equal(a, acc), mode
+        assert mode > 5 or torch.equal(got, rho), mode
