@@ -324,7 +324,7 @@ int pm_nu_set_background(pm_nu_ctx* ctx, int relativistic);
  *   series = 0 (default): the rational fit eq. (fit) of Appendix C;
  *   series = 1: the exact function of Appendix C, 4/(3 zeta(3)) sum_{n>=1} (-1)^{n+1}
  *     n/(n^2+x^2)^2: 12 terms and the Euler-Boole summation of the rest (relative error
- *     at most 1.4e-14 for every x).
+ *     below 2e-14).
  * The surrogate was trained with the fit and steps aside under the series. Sync.
  * Errors: PM_NU_EINVAL unless series is 0 or 1. */
 int pm_nu_set_kernel(pm_nu_ctx* ctx, int series);

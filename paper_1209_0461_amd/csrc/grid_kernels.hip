@@ -546,7 +546,7 @@ __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 
   bool side = true;                    // something of the chunk goes to the side grid
   if (patch || (npl > 0 && vol <= kSideBoxMax)) {
     if (patch) {
-      // register the patch in the coarse cells its box overlaps (origin and extents < 1024)
+      // register the patch in the coarse cells its box overlaps (origin and extents <= 512)
       const int64_t cells = static_cast<int64_t>(nc) * nc * nc;
       const int fx = gx0 >> cb_lg, fy = gy0 >> cb_lg, fz = gz0 >> cb_lg;
       const int4 entry = make_int4(static_cast<int>(chunk), gx0 | (gy0 << 10) | (gz0 << 20),
@@ -580,8 +580,10 @@ __global__ __launch_bounds__(NT, CAP <= kPatchTile ? 6 : CAP <= kPatchCap ? 4 : 
       if (patch) {
         // the patch (the box unpadded): consecutive lanes at consecutive nodes, four nodes per
         // thread per round with their LDS reads ahead of the stores. Node li of the pass lies
-        // in row li / ez and plane li / ez / ey; the FP32 quotients are exact (li < 2^14, and
-        // the fractional part of (li + 1/2) / e is at least 1 / (2e)).
+        // in row li / ez and plane li / ez / ey; the FP32 quotients are exact: (li + 1/2) / e
+        // lies at least 1 / (2e) from an integer, and its relative error of 2^-22 at most moves
+        // it by less for li < 2^20.
+        static_assert(TILE < (1 << 20), "nodes of a pass");
         unsigned long long* dst = pat + p0 * plane;
         const int tv = npp * plane, pad_z = sz - ez, pad_y = (sy - ey) * sz;
         const float inv_ez = 1.0f / static_cast<float>(ez), inv_ey = 1.0f / static_cast<float>(ey);
@@ -1179,7 +1181,7 @@ hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches,
                                 unsigned long long* rho_fb, int* n_fb,
                                 int64_t np, int nbox, int n, double inv_cell, int* flags,
                                 bool big_tile, hipStream_t s) {
-  if (n > 1024) return hipErrorInvalidValue;     // registry entries pack indices in 10 bits
+  if (n > 512) return hipErrorInvalidValue;      // registry entries pack extents up to n in 10 bits
   const int64_t chunks = layout.chunks;
   const dim3 grid(static_cast<unsigned>(chunks * nbox));
   const int ch = layout.particles;

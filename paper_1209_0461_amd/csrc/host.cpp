@@ -1090,7 +1090,6 @@ int pm_nu_side_grid_uses(pm_nu_ctx* ctx, int64_t* uses) {
   GET_CTX(ctx);
   if (!uses) return set_error(PM_NU_EINVAL, "uses is NULL");
   *uses = 0;
-  if (!c->n_fb) return PM_NU_OK;            // no patch deposit buffers (N < 64 by default)
   PMNU_HIP(hipStreamSynchronize(c->stream));
   unsigned total = 0;
   PMNU_HIP(hipMemcpy(&total, c->n_fb + 1, sizeof(unsigned), hipMemcpyDeviceToHost));

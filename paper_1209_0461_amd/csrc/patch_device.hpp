@@ -2,7 +2,7 @@
 // registry's sizes and the overlap of a patch with a region of a cell.
 //
 // A registry entry (int4) of a patch: x = chunk (patch slot), y = box origin
-// gx | gy << 10 | gz << 20, z = extents ex | ey << 10 | ez << 20 (each below 1024).
+// gx | gy << 10 | gz << 20, z = extents ex | ey << 10 | ez << 20 (each at most 512).
 #pragma once
 #include "pm_nu_internal.hpp"
 

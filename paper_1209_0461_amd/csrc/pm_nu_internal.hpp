@@ -168,14 +168,15 @@ struct Ctx {
   float2* tw = nullptr;            // [N] exp(-2 pi i m/N)
   float* inv_w2 = nullptr;         // [N] 1/sinc^4(pi n/N) per axis index (or 1)
   int* d_flags = nullptr;          // [1] bit 0: non-finite position seen
-  // patch deposit (deposit modes 6 and 7)
+  // patch deposit (deposit modes 6 to 9)
   unsigned long long* patches = nullptr;   // [nbox][patch.chunks][patch.slot] per-chunk patches
   PatchLayout patch;
   int* reg_count = nullptr;        // [nbox][coarse cells] patches registered
   int4* reg_list = nullptr;        // [nbox][coarse cells][32] (chunk, origin, extents, 0)
   unsigned long long* rho_fb = nullptr;    // [nbox][M] side grid, kept at zero
-  int* n_fb = nullptr;             // [2] chunks that used the side grid this deposit; running
-                                   // total of earlier deposits (added by the first FFT pass)
+  int* n_fb = nullptr;             // [3] chunks that used the side grid this deposit; running
+                                   // total of earlier deposits (added by the first FFT pass);
+                                   // finished workgroups of the running upload (d_up)
   unsigned fb_seen = 0;            // running total at the last pm_nu_side_grid_uses
   float* delta = nullptr;          // [nbox][M] delta in FP32 (modes 6, 7), or the density
   bool rho_clean = false;          // rho is zero (once the launched work has run)
@@ -253,8 +254,9 @@ static_assert(kMaxBins <= (1 << kRatioBinBits), "bin index of the packed ratio i
 constexpr int kPatchPad = 448;       // more room in the tile for padded strides (18 x 18 x 20)
 // up to one chunk per CU a workgroup has a CU to itself and takes most of its LDS
 constexpr int kPatchFewChunks = 256, kPatchFewTile = 18432;
-// largest box that goes to the side grid node by node: 8 nodes a particle, what the particles
-// would add one by one
+// largest box that goes to the side grid node by node, by its non-zero nodes alone: never more
+// atomics than the particles' own eight each, for the price of clearing and reading the tile once
+// for every kPatchTile nodes
 constexpr int kSideBoxMax = 8 * kPatchCH;
 hipError_t launch_fill_zero(void* p, int64_t bytes, hipStream_t s);
 hipError_t launch_extract_component(const float* src, float* dst, int64_t n, int comp,
@@ -370,7 +372,7 @@ hipError_t launch_surrogate_dataset(const RespBox* boxes, const double* pcdm, co
 int patch_cb_log2(int n);
 int64_t patch_coarse_cells(int n);
 // big_tile: the kPatchCap-node LDS tile (mode 7) instead of kPatchTile (mode 6); reg_list
-// entries are (chunk, packed box origin, packed extents, 0), n <= 1024
+// entries are (chunk, packed box origin, packed extents, 0), n <= 512
 hipError_t launch_deposit_patch(const float* pos, unsigned long long* patches,
                                 const PatchLayout& layout, int* reg_count, int4* reg_list,
                                 unsigned long long* rho_fb, int* n_fb,
