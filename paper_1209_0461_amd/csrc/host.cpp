@@ -1054,6 +1054,24 @@ int pm_nu_advance(pm_nu_ctx* ctx, float* pos, float* vel, float* acc, const doub
   return PM_NU_OK;
 }
 
+namespace {
+
+// The context's device is current while it lives: a kernel can only be launched there, and reading
+// results, which copies alone would do from any device, launches one.
+struct OnDevice {
+  int before = -1;
+  bool moved = false;
+  explicit OnDevice(const Ctx& c) {
+    moved = hipGetDevice(&before) == hipSuccess && before != c.device &&
+            hipSetDevice(c.device) == hipSuccess;
+  }
+  ~OnDevice() {
+    if (moved) (void)hipSetDevice(before);
+  }
+};
+
+}  // namespace
+
 int pm_nu_get_spectrum(pm_nu_ctx* ctx, int box, double* p_cdm, double* pnu_half,
                        double* ratio) {
   GET_CTX(ctx);
@@ -1070,6 +1088,7 @@ int pm_nu_get_spectrum(pm_nu_ctx* ctx, int box, double* p_cdm, double* pnu_half,
   {
     std::lock_guard<std::mutex> hold(c->spec_lock);   // readers of the same context
     const double* h = c->h_spec;
+    const OnDevice here(*c);
     hipError_t e = launch_read_spectrum(c->pcdm + box * B, c->pnu + box * B, c->ratio + box * B,
                                         c->d_flags, c->B, c->h_spec, c->stream);
     if (e != hipSuccess) return set_error(PM_NU_EHIP, "read spectrum: %s", hipGetErrorString(e));
